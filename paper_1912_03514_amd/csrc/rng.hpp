@@ -69,14 +69,13 @@ __device__ __forceinline__ void gaussian_block(uint32_t seed, uint64_t stream, u
   const U32x4 w = philox4x32_10((uint32_t)blk, (uint32_t)(blk >> 32), (uint32_t)stream,
                                 (uint32_t)(stream >> 32), seed, 0u);
   const double two32inv = 2.3283064365386963e-10;  // 2^-32
-  const double twopi = 6.283185307179586;           // 2 pi rounded to double
 #pragma unroll
   for (int p = 0; p < 2; ++p) {
     const double ua = ((double)w.v[2 * p] + 0.5) * two32inv;
     const double ub = ((double)w.v[2 * p + 1] + 0.5) * two32inv;
     const double rad = sqrt(-2.0 * log(ua));
     double s, c;
-    sincos(twopi * ub, &s, &c);
+    sincospi(2.0 * ub, &s, &c);
     out[2 * p] = rad * c;
     out[2 * p + 1] = rad * s;
   }

@@ -4,7 +4,9 @@
 // path, BF16 MFMA with FP32 accumulation for the mixed path).
 #include <math.h>
 
-#include "device_util.hpp"
+#include <type_traits>
+
+#include "gemm64.hpp"
 #include "internal.hpp"
 #include "rng.hpp"
 
@@ -14,7 +16,6 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------------------
 // BF16 rounding (round to nearest even of the exact value).  A double is first
@@ -572,12 +573,15 @@ __global__ __launch_bounds__(kBlock) void cs_accum_kernel(const TA* __restrict__
 }
 
 // ---------------------------------------------------------------------------
-// Gaussian:  S (M x K, row stride lds) with S_ij = N(0,1) * scale drawn from
-// Philox element i*K + j; stored as double (plain) or BF16 bits (mixed).
-// Columns K..lds-1 are zero.
+// Gaussian:  S (M x K) with S_ij = N(0,1) * scale drawn from Philox element
+// i*K + j.  FP64 S (plain) is laid out in panels of 16 k (element (i, k) at
+// (k / 16) * 16 M + 16 i + k % 16: a step's tile of the product is one
+// contiguous range), BF16 bits (mixed) row-major with row stride lds.  Columns
+// K .. kpad-1 (kpad = lds, or K rounded up to 16) are zero: the thread that
+// draws a row's last entry writes them.
 // ---------------------------------------------------------------------------
 template <typename TSel>
-__global__ void gauss_gen_kernel(TSel* S, int64_t M, int64_t K, int64_t lds, uint32_t seed,
+__global__ void gauss_gen_kernel(TSel* S, int64_t M, int64_t K, int64_t kpad, uint32_t seed,
                                  uint64_t stream, double scale) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;  // one Philox block each
   const int64_t total = M * K;
@@ -592,95 +596,108 @@ __global__ void gauss_gen_kernel(TSel* S, int64_t M, int64_t K, int64_t lds, uin
   else
     gaussian_block_f32(seed, stream, (uint64_t)e, zf);
   const float scale_f = (float)scale;
-  // row and column of the first element (one 64-bit division per thread), then
-  // step along the row with wrap-around
-  int64_t i = first / K, j = first - i * K;
+  auto at = [&](int64_t i, int64_t j) {
+    return sizeof(TSel) == 8 ? (j / kGemmK) * kGemmK * M + i * kGemmK + j % kGemmK : i * kpad + j;
+  };
+  // row and column of the first element (one division per thread, 32-bit where the index
+  // allows it), then step along the row with wrap-around
+  int64_t i, j;
+  if (total <= 0xFFFFFFFFll) {
+    i = (uint32_t)first / (uint32_t)K;
+    j = (uint32_t)first - (uint32_t)i * (uint32_t)K;
+  } else {
+    i = first / K;
+    j = first - i * K;
+  }
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
     if (first + t < total) {
       if constexpr (sizeof(TSel) == 8) {
-        S[i * lds + j] = z[t] * scale;
+        S[at(i, j)] = z[t] * scale;
       } else {
-        S[i * lds + j] = bf16_rne(zf[t] * scale_f);
+        S[at(i, j)] = bf16_rne(zf[t] * scale_f);
       }
-    }
-    if (++j == K) {
-      j = 0;
-      ++i;
+      if (++j == K) {
+        for (; j < kpad; ++j) S[at(i, j)] = TSel(0);
+        j = 0;
+        ++i;
+      }
     }
   }
 }
 
-__global__ void zero_pad_cols(void* S, int elem, int64_t M, int64_t K, int64_t lds) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t padw = lds - K;
-  if (padw <= 0 || e >= M * padw) return;
-  const int64_t i = e / padw, j = K + e % padw;
-  if (elem == 8)
-    ((double*)S)[i * lds + j] = 0.0;
-  else
-    ((uint16_t*)S)[i * lds + j] = 0;
-}
-
-// P[z] (M x N) = S[:, kz] B[kz, :] in FP64 on the matrix cores
-// (v_mfma_f64_16x16x4: A operand lane l = row l%16, k l/16; B operand lane l =
-// col l%16, k l/16; result register r of lane l is row l/16 + 4r, column l%16).
-template <typename TS, typename TB>
-__global__ __launch_bounds__(kBlock) void gemm_f64_kernel(const TS* __restrict__ S, int64_t lds,
+// P[z] (M x N) = X[:, kz] Y[kz, :], one 64 x BN tile per workgroup (gemm64.hpp); X by
+// operand type (FP64 panels of S, or the rows of A), Y k-major.
+template <typename OX, typename OY, int BN, typename TX, typename TY>
+__global__ __launch_bounds__(kBlock) void gemm_f64_kernel(const TX* __restrict__ X, int64_t ldx,
                                                           int64_t M, int64_t K,
-                                                          const TB* __restrict__ B, int64_t ldb,
+                                                          const TY* __restrict__ Y, int64_t ldy,
                                                           int64_t N, int64_t kchunk,
                                                           double* __restrict__ P) {
-  constexpr int BM = 64, BN = 64, BK = 16;
-  __shared__ double Ss[BM][BK + 1];
-  __shared__ double Bs[BK][BN + 1];
-  const int64_t m0 = (int64_t)blockIdx.y * BM, n0 = (int64_t)blockIdx.x * BN;
+  constexpr int BM = 64;
+  __shared__ __attribute__((aligned(16))) double lds[gemm64_lds<OX, OY>()];
+  const int64_t m0 = (int64_t)blockIdx.x * BM, n0 = (int64_t)blockIdx.y * BN;
   const int64_t kb = (int64_t)blockIdx.z * kchunk, ke = min(K, kb + kchunk);
+  f64x4 acc[BM / 32][BN / 32];
+  gemm64_tile<OX, OY, BM, BN>(X, ldx, m0, M, Y, ldy, n0, N, kb, ke, lds, acc);
   const int lane = lane_id(), wave = wave_id();
-  const int wr = wave >> 1, wc = wave & 1;
-  f64x4 acc[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = (f64x4){0.0, 0.0, 0.0, 0.0};
-  for (int64_t k0 = kb; k0 < ke; k0 += BK) {
-    for (int e = threadIdx.x; e < BM * BK; e += kBlock) {
-      const int r = e / BK, c = e % BK;
-      const int64_t gr = m0 + r, gk = k0 + c;
-      Ss[r][c] = (gr < M && gk < ke) ? (double)S[gr * lds + gk] : 0.0;
-    }
-    for (int e = threadIdx.x; e < BK * BN; e += kBlock) {
-      const int r = e / BN, c = e % BN;
-      const int64_t gk = k0 + r, gc = n0 + c;
-      Bs[r][c] = (gk < ke && gc < N) ? (double)B[gk * ldb + gc] : 0.0;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < BK; kk += 4) {
-      double a[2], b[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) a[i] = Ss[wr * 32 + i * 16 + (lane & 15)][kk + (lane >> 4)];
-#pragma unroll
-      for (int j = 0; j < 2; ++j) b[j] = Bs[kk + (lane >> 4)][wc * 32 + j * 16 + (lane & 15)];
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
-    }
-    __syncthreads();
-  }
   double* Pz = P + (int64_t)blockIdx.z * M * N;
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int a = 0; a < BM / 32; ++a)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int b = 0; b < BN / 32; ++b)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int64_t row = m0 + wr * 32 + i * 16 + (lane >> 4) + 4 * r;
-        const int64_t col = n0 + wc * 32 + j * 16 + (lane & 15);
-        if (row < M && col < N) Pz[row * N + col] = acc[i][j][r];
+        const int64_t row = m0 + (wave >> 1) * (BM / 2) + 16 * a + (lane >> 4) + 4 * r;
+        const int64_t col = n0 + (wave & 1) * (BN / 2) + 16 * b + (lane & 15);
+        if (row < M && col < N) Pz[row * N + col] = acc[a][b][r];
       }
+}
+
+// y[r] = A[r, :] . w, four rows per wave: each 16 bytes of w serve four of A.  Bound by
+// the one read of A (2^16 x 4096 FP64: 0.35 ms at the ~6 TB/s of a read stream; as a 64-wide
+// matrix product with one useful column it took 1.24 ms).
+template <typename TA>
+__global__ __launch_bounds__(kBlock) void rowdot_kernel(const TA* __restrict__ A, int64_t n,
+                                                        int64_t d, int64_t lda,
+                                                        const double* __restrict__ w,
+                                                        double* __restrict__ y) {
+  constexpr int R = 4, V = 16 / (int)sizeof(TA);
+  const int lane = lane_id();
+  const int64_t r0 = ((int64_t)blockIdx.x * kWavesPerBlock + wave_id()) * R;
+  if (r0 >= n) return;
+  const TA* row[R];
+  double acc[R];
+#pragma unroll
+  for (int t = 0; t < R; ++t) {
+    row[t] = A + min(r0 + t, n - 1) * lda;
+    acc[t] = 0.0;
+  }
+  int64_t c = (int64_t)lane * V;
+#pragma unroll 2
+  for (; c + V <= d; c += kWave * V) {
+    TA a[R][V];
+    double wv[V];
+#pragma unroll
+    for (int t = 0; t < R; ++t) VecLoad<TA, V, true>::run(row[t] + c, a[t]);
+#pragma unroll
+    for (int q = 0; q < V; ++q) wv[q] = w[c + q];
+#pragma unroll
+    for (int t = 0; t < R; ++t)
+#pragma unroll
+      for (int q = 0; q < V; ++q) acc[t] += (double)a[t][q] * wv[q];
+  }
+#pragma unroll
+  for (int q = 0; q < V; ++q)
+    if (c + q < d) {
+#pragma unroll
+      for (int t = 0; t < R; ++t) acc[t] += (double)row[t][c + q] * w[c + q];
+    }
+#pragma unroll
+  for (int t = 0; t < R; ++t) {
+    const double s = wave_sum(acc[t]);
+    if (lane == 0 && r0 + t < n) y[r0 + t] = s;
+  }
 }
 
 // Bt (N x ldbt, BF16 bits) = B^T rounded to BF16 (round to nearest even of the
@@ -856,10 +873,13 @@ template <typename TP, typename TOut>
 __global__ void splitk_reduce_kernel(const TP* P, int splits, int64_t M, int64_t N, TOut* out,
                                      int64_t ldo) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= M * N) return;
+  const int64_t MN = M * N;
+  if (e >= MN) return;
   double s = 0.0;
-  for (int z = 0; z < splits; ++z) s += (double)P[(int64_t)z * M * N + e];
-  out[(e / N) * ldo + (e % N)] = (TOut)s;
+#pragma unroll 8
+  for (int z = 0; z < splits; ++z) s += (double)P[z * MN + e];
+  const int64_t r = MN <= 0xFFFFFFFFll ? (int64_t)((uint32_t)e / (uint32_t)N) : e / N;
+  out[r * ldo + (e - r * N)] = (TOut)s;
 }
 
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
@@ -867,7 +887,7 @@ inline bool hip_ok() { return hipGetLastError() == hipSuccess; }
 
 // ---- Gaussian sketch driver -------------------------------------------------
 struct GaussPlan {
-  int64_t lds;     // padded row stride of S
+  int64_t lds;     // padded columns of S (its row stride when BF16)
   int splits;
   int64_t kchunk;
   int64_t ldbt;    // row stride of the BF16 transpose of B (mixed)
@@ -880,14 +900,19 @@ GaussPlan gauss_plan(const mihs_handle* h, int64_t M, int64_t K, int64_t N, int 
                      int terms = 1) {
   GaussPlan g;
   g.terms = mixed ? terms : 1;
-  const int BM = mixed ? 128 : 64, BN = mixed ? 128 : 64, BK = mixed ? 64 : 16;
-  g.lds = (K + 7) / 8 * 8;
+  const int BM = mixed ? 128 : 64, BN = mixed ? 128 : 64, BK = mixed ? 64 : kGemmK;
+  g.lds = mixed ? (K + 7) / 8 * 8 : (K + kGemmK - 1) / kGemmK * kGemmK;
   const int64_t tiles = ceil_div(M, BM) * ceil_div(N, BN);
-  int64_t want = ceil_div(2 * (int64_t)h->num_cu, tiles);
-  const int64_t kmax = ceil_div(K, 8 * BK);  // keep >= 8 k-steps per split
+  // mixed: two workgroups per CU and >= 8 steps per split.  FP64: four per CU (they fill
+  // each other's operand waits: 1400 x 30011 x 700, 242 tiles, 1852 us whole, 1148 in 4
+  // splits, 1119 in 8) and >= 4 steps (200 x 1500 x 61, 4 tiles: 14.4 us in 8 splits, 7.1
+  // in 24); at most 32, as every split is written and read back once.
+  const int64_t most = mixed ? 64 : 32;
+  int64_t want = ceil_div((mixed ? 2 : 4) * (int64_t)h->num_cu, tiles);
+  const int64_t kmax = ceil_div(K, (mixed ? 8 : 4) * BK);
   if (want > kmax) want = kmax;
+  if (want > most) want = most;
   if (want < 1) want = 1;
-  if (want > 64) want = 64;
   g.kchunk = ceil_div(ceil_div(K, want), BK) * BK;
   g.splits = (int)ceil_div(K, g.kchunk);
   g.s_bytes = align_up((size_t)M * g.lds * (mixed ? 2 : 8), 256);
@@ -915,9 +940,6 @@ int run_gauss(const mihs_handle* h, const TB* B, int64_t K, int64_t N, int64_t l
   else
     hipLaunchKernelGGL(gauss_gen_kernel<double>, dim3((unsigned)ceil_div(nblk, 256)), dim3(256), 0,
                        st, (double*)S, M, K, g.lds, seed, stream_id, scale);
-  if (g.lds > K)
-    hipLaunchKernelGGL(zero_pad_cols, dim3((unsigned)ceil_div(M * (g.lds - K), 256)), dim3(256), 0,
-                       st, S, mixed ? 2 : 8, M, K, g.lds);
   if (!hip_ok()) return MIHS_ERR_HIP;
   if (mixed) {
     uint16_t* Bt = (uint16_t*)(ws + g.s_bytes + g.p_bytes);
@@ -946,9 +968,10 @@ int run_gauss(const mihs_handle* h, const TB* B, int64_t K, int64_t N, int64_t l
                        dim3(256), 0, st, (const float*)P, g.terms * g.splits, M, N, (float*)out,
                        ldo);
   } else {
-    dim3 grid((unsigned)ceil_div(N, 64), (unsigned)ceil_div(M, 64), (unsigned)g.splits);
-    hipLaunchKernelGGL((gemm_f64_kernel<double, TB>), grid, dim3(kBlock), 0, st, (const double*)S, g.lds, M,
-                       K, B, ldb, N, g.kchunk, (double*)P);
+    dim3 grid((unsigned)ceil_div(M, 64), (unsigned)ceil_div(N, 64), (unsigned)g.splits);
+    hipLaunchKernelGGL((gemm_f64_kernel<KPanel<double, 64>, KRows<TB, 64>, 64, double, TB>), grid,
+                       dim3(kBlock), 0, st, (const double*)S, M, M, K, B, ldb, N, g.kchunk,
+                       (double*)P);
     hipLaunchKernelGGL((splitk_reduce_kernel<double, double>), dim3((unsigned)ceil_div(M * N, 256)),
                        dim3(256), 0, st, (const double*)P, g.splits, M, N, (double*)out, ldo);
   }
@@ -1137,18 +1160,40 @@ int launch_fill(double* p, double value, int64_t count, hipStream_t st) {
   return hip_ok() ? MIHS_OK : MIHS_ERR_HIP;
 }
 
+template <typename TA>
+static void apply_rows(const TA* A, int64_t n, int64_t d, int64_t lda, const double* W, int64_t k,
+                       double* Y, hipStream_t st) {
+  if (k == 1) {
+    hipLaunchKernelGGL(rowdot_kernel<TA>, dim3((unsigned)ceil_div(n, 4 * kWavesPerBlock)),
+                       dim3(kBlock), 0, st, A, n, d, lda, W, Y);
+    return;
+  }
+  // W's rows start on 16-byte boundaries when k is even and W itself does
+  const bool vec = k % 2 == 0 && ((uintptr_t)W & 15) == 0;
+  auto go = [&](auto ox, auto oy, auto bn) {
+    constexpr int BN = decltype(bn)::value;
+    hipLaunchKernelGGL((gemm_f64_kernel<decltype(ox), decltype(oy), BN, TA, double>),
+                       dim3((unsigned)ceil_div(n, 64), (unsigned)ceil_div(k, BN), 1), dim3(kBlock),
+                       0, st, A, lda, n, d, W, k, k, d, Y);
+  };
+  const std::integral_constant<int, 32> b32;
+  const std::integral_constant<int, 64> b64;
+  // up to 32 columns a 32-wide tile multiplies less padding
+  if (k <= 32 && vec) go(KCols<TA, 64>(), KRows<double, 32, true>(), b32);
+  else if (k <= 32) go(KCols<TA, 64>(), KRows<double, 32, false>(), b32);
+  else if (vec) go(KCols<TA, 64>(), KRows<double, 64, true>(), b64);
+  else go(KCols<TA, 64>(), KRows<double, 64, false>(), b64);
+}
+
 int launch_apply_rows(const mihs_handle* h, const void* A, int a_f32, int64_t n, int64_t d,
                       int64_t lda, const double* W, int64_t k, double* Y, int64_t ldy,
                       hipStream_t st) {
   (void)h;
   if (ldy != k) return MIHS_ERR_UNSUPPORTED;
-  dim3 grid((unsigned)ceil_div(k, 64), (unsigned)ceil_div(n, 64), 1);
   if (a_f32)
-    hipLaunchKernelGGL((gemm_f64_kernel<float, double>), grid, dim3(kBlock), 0, st,
-                       (const float*)A, lda, n, d, W, k, k, d, Y);
+    apply_rows((const float*)A, n, d, lda, W, k, Y, st);
   else
-    hipLaunchKernelGGL((gemm_f64_kernel<double, double>), grid, dim3(kBlock), 0, st,
-                       (const double*)A, lda, n, d, W, k, k, d, Y);
+    apply_rows((const double*)A, n, d, lda, W, k, Y, st);
   return hip_ok() ? MIHS_OK : MIHS_ERR_HIP;
 }
 

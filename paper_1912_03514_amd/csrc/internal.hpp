@@ -96,10 +96,6 @@ struct SolveDesc {
   // 1: the Gram matrix of SA is already in this workspace (an earlier call with
   // the same SA and workspace formed it)
   int gram_ready = 0;
-  // launch shape; 0 = chosen from the sizes: workgroups of the inner-solve
-  // group, and the fewest rows of A per workgroup
-  int cg_groups = 0;
-  int64_t rows_per_wg = 0;
 };
 
 // g = A^T (c - A x) + rhs - lambda x (c and rhs may be null) for A n x d, d <= 4096;

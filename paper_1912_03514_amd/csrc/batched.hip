@@ -27,6 +27,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <type_traits>
 #include <vector>
 
 #include "device_util.hpp"
@@ -81,9 +82,9 @@ struct BatchArgs {
 };
 
 // Scratch of one entry, in doubles: partial block vectors of every team member,
-// then R, Z, Q, XP (dp x KR each), then scalar partial slots.
+// then R, Z, Q, XP (dp x KR each), then scalar partial slots and tagged sums.
 struct EntryLayout {
-  size_t part, R, Z, Q, XP, scal, total;
+  size_t part, R, Z, Q, XP, scal, tag, total;
 };
 __host__ __device__ inline EntryLayout entry_layout(int dp, int tsize) {
   EntryLayout L;
@@ -95,6 +96,7 @@ __host__ __device__ inline EntryLayout entry_layout(int dp, int tsize) {
   L.Q = o; o += blk;
   L.XP = o; o += blk;
   L.scal = o; o += (size_t)tsize * kNScal;
+  L.tag = o; o += (size_t)tsize * 2 * KR;  // tagged per-column sums (team CG)
   L.total = (o + 31) / 32 * 32;
   return L;
 }
@@ -920,49 +922,74 @@ __device__ __attribute__((noinline)) int64_t cg_solve_local(const TH* __restrict
   return k;
 }
 
+// Sum over the members' slots of column tid % 16, to every thread: the members' loads are
+// one round trip (a serial loop over 15 members took most of the 40 us of a CG step at
+// d = 486).  buf: kBlock doubles of LDS that no thread still reads.
+__device__ __forceinline__ double member_sums(const double* slots, int Tc, double* buf) {
+  const int j = threadIdx.x % KR, q = threadIdx.x / KR;
+  double v = 0.0;
+  for (int m = q; m < Tc; m += kBlock / KR) v += co_load(slots + (int64_t)m * kNScal + j);
+  buf[threadIdx.x] = v;
+  __syncthreads();
+  double s = buf[j];
+#pragma unroll
+  for (int i = 1; i < kBlock / KR; ++i) s += buf[i * KR + j];
+  return s;
+}
+
 // The one-workgroup CG above spread over a sub-team of Tc workgroups (rank
 // 0 .. Tc - 1 of the problem's team).  The 16-row blocks are grouped in fours
 // (a quad: one block per wave, as above), and member `rank` owns quads
 // rank, rank + Tc, ...: each of its waves forms whole rows of H p for its own
-// blocks from the same register ring, and keeps r and z of its rows in
-// registers.  Per step, two sub-team barriers: one after each member has
-// stored its per-column sums p . q (scalar slots), one after it has stored its
-// rows of the new r and its per-column sums r . r; every member then reads the
-// whole r back and forms the whole p = r + beta p in LDS for the next
-// products.  Every member sums the slots in member order, so all of them take
-// the same step lengths, masks and stop decision.  A last barrier publishes
-// the members' rows of z to the row owners of the heavy-ball update.  With two
-// or more members a member owns at most half the quads, so its r and z take
-// half the registers of the one-workgroup form.  Returns the number of steps
-// (the caller advances its barrier epoch by 2 k + 1), or -1 if a barrier timed
-// out.
-template <typename TH, int DP>
+// blocks and keeps r, z and q of its rows in registers.  RES: one quad per
+// member at most (or, KSP = 2, half a quad: two waves share a block, one taking
+// the even k-chunks and one the odd, and the first keeps the block's vectors),
+// whose rows of H stay in registers for the whole solve (at
+// d = 277 a product took 6 us through the ring, whose loads queue behind the
+// step's exchanges, against 1.9 us of matrix-core time); otherwise H streams
+// through the register ring.  Per step, two exchanges: the members' per-column
+// sums p . q, tagged (no barrier), and a sub-team barrier once each has stored
+// its rows of the new r and its per-column sums r . r; every member then reads
+// the whole r back, all its loads in flight together (one at a time they took
+// about 25 of the 40 us of a step at d = 486), and forms the whole
+// p = r + beta p in LDS for the next products.  Every member adds the sums in
+// the same order, so all of them take the same step lengths, masks and stop
+// decision.  A last barrier publishes the members' rows of z to the row owners
+// of the heavy-ball update.  Returns the number of steps (the caller advances
+// its barrier epoch by k + 1), or -1 if a wait timed out.
+template <typename TH, int DP, bool RES, int KSP>
 __device__ __attribute__((noinline)) int64_t cg_solve_team(
     const TH* __restrict__ H, int64_t ldh, int d, int rank, int Tc, double* R, double* Z,
-    const double* scal, double* myscal, unsigned* bar_cg, unsigned epoch, int* err,
+    const double* scal, double* myscal, tagged_t* tags, unsigned* bar_cg, unsigned epoch, int* err,
     BarrierSpin spin, double eps_sub, int64_t max_inner) {
   extern __shared__ uint4 lds_raw[];
   double* stage = (double*)lds_raw;      // p, DP x 16 (all rows)
-  double* ql = stage + DP * KR;          // q, DP x 16 (this member's rows)
   double* red0 = (double*)((char*)lds_raw + kUredOffset);
   double* red1 = red0 + kBlock;
+  double* red2 = red1 + kBlock;
+  double* red3 = red2 + kBlock;
   Shared& sh = g_sh;
   typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
   typedef const u32x4 __attribute__((address_space(1)))* gvec;
-  constexpr int NBW = DP / 128 > 0 ? DP / 128 : 1;  // quads per member (Tc >= 2)
+  // quads per member: one (RES), or with two or more members at most half of them
+  constexpr int NBW = !RES && DP / 128 > 0 ? DP / 128 : 1;
   constexpr int NV = 4 * NBW;
   constexpr int VE = 16 / (int)sizeof(TH);
   constexpr int KQ = DP / 4;
   constexpr int NLD = (KQ * (int)sizeof(TH) / 16) < 4 ? KQ * (int)sizeof(TH) / 16 : 4;
   constexpr int CE = NLD * VE;
-  constexpr int NRING = 4;
+  constexpr int NCH = KQ / CE;             // chunks of one row
+  constexpr int NRING = RES ? (NCH + KSP - 1) / KSP : 4;
+  static_assert(RES || KSP == 1, "the ring holds whole rows");
   const int lane = lane_id(), wave = wave_id();
   const int j = lane & 15, g = lane >> 4;
   const int tid = (int)threadIdx.x;
-  // this wave's blocks: 4 (rank + Tc b) + wave for b < nbw (those starting below d)
-  auto block_row0 = [&](int b) { return 16 * (4 * (rank + Tc * b) + wave); };
+  const int half = wave % KSP;  // share of the k-chunks
+  // this wave's blocks for b < nbw (those starting below d)
+  auto block_row0 = [&](int b) { return 16 * (4 / KSP * (rank + Tc * b) + wave / KSP); };
   int nbw = 0;
   while (nbw < NBW && block_row0(nbw) < d) ++nbw;
+  const int nrw = half == 0 ? nbw : 0;  // blocks whose r, z and q this wave keeps
   const int nch = min(KQ / CE, (d + 4 * CE - 1) / (4 * CE));
   const int T = nbw * nch;
   const int Tp = T > 0 ? (T + NRING - 1) / NRING * NRING : 0;
@@ -989,13 +1016,25 @@ __device__ __attribute__((noinline)) int64_t cg_solve_team(
   };
   Chunk ring[NRING];
 #pragma unroll
-  for (int u = 0; u < NRING; ++u) fetch(ring[u]);
+  for (int u = 0; u < NRING; ++u) {
+    if constexpr (RES) {
+      const int c = u * KSP + half;  // a slot past the last chunk reads row j (never used)
+      const bool in = nbw > 0 && c < nch;
+      const gvec src = (gvec)(H + (int64_t)(in ? block_row0(0) + j : j) * ldh +
+                              (in ? c : 0) * 4 * CE + g * CE);
+#pragma unroll
+      for (int i = 0; i < NLD; ++i) ring[u].u[i] = src[i];
+    } else {
+      fetch(ring[u]);
+    }
+  }
 
-  double r[NV], z[NV];
+  double r[NV], z[NV], q[NV];
 #pragma unroll
   for (int v = 0; v < NV; ++v) {
     const int row = row_of(v);
-    r[v] = ((v >> 2) < nbw && row < d) ? co_load(R + row * KR + j) : 0.0;
+    q[v] = 0.0;
+    r[v] = ((v >> 2) < nrw && row < d) ? co_load(R + row * KR + j) : 0.0;
     z[v] = 0.0;
   }
   const double lj = sh.lam[j];
@@ -1010,43 +1049,85 @@ __device__ __attribute__((noinline)) int64_t cg_solve_team(
     if (!any || k >= max_inner) break;
     // p = r (first step) or r + beta_cg p over all rows, r as published by
     // the members; inactive columns carry p = 0
-    for (int idx = tid; idx < DP * KR; idx += kBlock) {
-      const int c = idx / KR;  // column idx % KR == j for this thread
-      double v = 0.0;
-      if (c < d && act) v = (k == 0) ? co_load(R + idx) : co_load(R + idx) + bc * stage[idx];
-      stage[idx] = v;
+    constexpr int NP = DP * KR / kBlock;       // entries per thread
+    constexpr int NF = NP < 32 ? NP : 32;      // loads in flight
+#pragma unroll
+    for (int i0 = 0; i0 < NP; i0 += NF) {
+      double rv[NF];
+#pragma unroll
+      for (int i = 0; i < NF; ++i) {
+        const int idx = (i0 + i) * kBlock + tid;  // column idx % KR == j for this thread
+        rv[i] = (idx / KR < d && act) ? co_load(R + idx) : 0.0;
+      }
+#pragma unroll
+      for (int i = 0; i < NF; ++i) {
+        const int idx = (i0 + i) * kBlock + tid;
+        // (bc of the first step is 0 but the stage holds no p yet)
+        stage[idx] = (k == 0 || !act) ? rv[i] : rv[i] + bc * stage[idx];
+      }
     }
     __syncthreads();
     // q = H p + lambda p on this member's blocks, p . q per column
     double pq = 0.0;
     {
       f64x4 acc = {0.0, 0.0, 0.0, 0.0};
-      int b = 0, c = 0;
-      for (int t0 = 0; t0 < Tp; t0 += NRING) {
+      auto finish = [&](int b) {  // the block's rows are done: q and p . q
 #pragma unroll
-        for (int u = 0; u < NRING; ++u) {
-          if (t0 + u < T) {
-            const double* pk = stage + (c * 4 * CE + g * CE) * KR + j;
+        for (int bb = 0; bb < NBW; ++bb)
+          if (bb == b) {
 #pragma unroll
-            for (int e = 0; e < CE; ++e)
-              acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)ring[u].v[e], pk[e * KR], acc,
-                                                         0, 0, 0);
-            if (++c == nch) {
-              const int row0 = block_row0(b) + g;
-#pragma unroll
-              for (int i = 0; i < 4; ++i) {
-                const int o = (row0 + 4 * i) * KR + j;
-                const double pv = stage[o];
-                const double qv = acc[i] + lj * pv;
-                ql[o] = qv;
-                pq += pv * qv;
-              }
-              acc = (f64x4){0.0, 0.0, 0.0, 0.0};
-              c = 0;
-              ++b;
+            for (int i = 0; i < 4; ++i) {
+              const double pv = stage[row_of(4 * bb + i) * KR + j];
+              q[4 * bb + i] = acc[i] + lj * pv;
+              pq += pv * q[4 * bb + i];
             }
           }
-          fetch(ring[u]);
+      };
+      if constexpr (RES) {
+        if (nbw > 0) {
+#pragma unroll
+          for (int u = 0; u < NRING; ++u) {
+            const int c = u * KSP + half;
+            if (c < nch) {
+              const double* pk = stage + (c * 4 * CE + g * CE) * KR + j;
+#pragma unroll
+              for (int e = 0; e < CE; ++e)
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)ring[u].v[e], pk[e * KR], acc,
+                                                           0, 0, 0);
+            }
+          }
+        }
+        if constexpr (KSP == 2) {  // the second half's sums (red1, red2 are free here)
+          double* xb = red1 + (wave / 2) * kBlock;
+          if (half)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) xb[i * kWave + lane] = acc[i];
+          __syncthreads();
+          if (!half)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[i] += xb[i * kWave + lane];
+        }
+        if (nrw > 0) finish(0);
+      } else {
+        int b = 0, c = 0;
+        for (int t0 = 0; t0 < Tp; t0 += NRING) {
+#pragma unroll
+          for (int u = 0; u < NRING; ++u) {
+            if (t0 + u < T) {
+              const double* pk = stage + (c * 4 * CE + g * CE) * KR + j;
+#pragma unroll
+              for (int e = 0; e < CE; ++e)
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)ring[u].v[e], pk[e * KR], acc,
+                                                           0, 0, 0);
+              if (++c == nch) {
+                finish(b);
+                acc = (f64x4){0.0, 0.0, 0.0, 0.0};
+                c = 0;
+                ++b;
+              }
+            }
+            fetch(ring[u]);
+          }
         }
       }
     }
@@ -1056,11 +1137,25 @@ __device__ __attribute__((noinline)) int64_t cg_solve_team(
       double s = 0.0;
 #pragma unroll
       for (int t = 0; t < 16; ++t) s += red0[t * 16 + tid];
-      co_store(myscal + KR + tid, s);
+      tagged_put(tags + ((int64_t)rank * KR + tid) * 2, s, epoch + 1u);
     }
-    if (!group_sync(bar_cg, Tc, epoch, err, &sh.flag, spin)) return -1;
-    double spq = 0.0;
-    for (int m = 0; m < Tc; ++m) spq += co_load(scal + (int64_t)m * kNScal + KR + j);
+    // the sums p . q travel tagged (the barrier of the new r below keeps a step's words
+    // until everybody has read them)
+    double spq;
+    {
+      double v = 0.0;
+      for (int m = tid / KR; m < Tc; m += kBlock / KR) {
+        double x = 0.0;
+        if (!tagged_get(tags + ((int64_t)m * KR + j) * 2, epoch + 1u, x, err, spin)) sh.flag = 0;
+        v += x;
+      }
+      red2[tid] = v;
+      __syncthreads();
+      if (!sh.flag) return -1;
+      spq = red2[j];
+#pragma unroll
+      for (int i = 1; i < kBlock / KR; ++i) spq += red2[i * KR + j];
+    }
     double al = 0.0;
     if (act) {
       al = rr / spq;
@@ -1072,12 +1167,12 @@ __device__ __attribute__((noinline)) int64_t cg_solve_team(
     double rrp = 0.0;
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
-      if ((v >> 2) < nbw) {
+      if ((v >> 2) < nrw) {
         const int row = row_of(v);
         const int o = row * KR + j;
         if (act) {
           z[v] += al * stage[o];
-          r[v] -= al * ql[o];
+          r[v] -= al * q[v];
         }
         if (row < d) co_store(R + o, r[v]);
       }
@@ -1092,8 +1187,7 @@ __device__ __attribute__((noinline)) int64_t cg_solve_team(
       co_store(myscal + tid, s);
     }
     if (!group_sync(bar_cg, Tc, epoch, err, &sh.flag, spin)) return -1;
-    double rn = 0.0;
-    for (int m = 0; m < Tc; ++m) rn += co_load(scal + (int64_t)m * kNScal + j);
+    const double rn = member_sums(scal, Tc, red3);
     ++k;
     if (act) {
       bc = rn / rr;
@@ -1108,7 +1202,7 @@ __device__ __attribute__((noinline)) int64_t cg_solve_team(
 #pragma unroll
   for (int v = 0; v < NV; ++v) {
     const int row = row_of(v);
-    if ((v >> 2) < nbw && row < d) co_store(Z + row * KR + j, z[v]);
+    if ((v >> 2) < nrw && row < d) co_store(Z + row * KR + j, z[v]);
   }
   __builtin_amdgcn_s_waitcnt(0);  // the ring's look-ahead loads too
   if (!group_sync(bar_cg, Tc, epoch, err, &sh.flag, spin)) return -1;
@@ -1233,14 +1327,50 @@ __device__ __attribute__((noinline)) void tri_solve_local(const double* __restri
   __syncthreads();
 }
 
+// How many waves share a 16-row block of a team CG, and so the rows a member takes (64 /
+// waves): two where the sub-team is large enough for half the rows each (the products take
+// half the time, and FP64 rows of 1024 entries fit the registers), else one.  0: this entry
+// does not run the team form (a sub-team of one, or 1024-wide rows that do not fit).
+template <int DP>
+__device__ __forceinline__ int team_split(const BatchArgs& a, const BatchEntry& e) {
+  if (e.tcg < 2 || (size_t)DP * KR * sizeof(double) > kUredOffset) return 0;
+  if (e.tcg >= (e.d + 31) / 32 && e.d > 32) return 2;
+  if (DP <= 512) return 1;
+  return a.h_f32 && e.tcg >= (e.d + 63) / 64 ? 1 : 0;
+}
+
+template <int DP, typename TH>
+__device__ __forceinline__ int64_t team_solve(const BatchArgs& a, const BatchEntry& e, int split,
+                                              int rank, int Tc, double* R, double* Z,
+                                              const double* scal, double* myscal, tagged_t* tags,
+                                              unsigned ep) {
+  const TH* H = (const TH*)e.H;
+  auto go = [&](auto res, auto ksp) {
+    return cg_solve_team<TH, DP, decltype(res)::value, decltype(ksp)::value>(
+        H, e.ldh, e.d, rank, Tc, R, Z, scal, myscal, tags, e.bar_cg, ep, a.err, a.spin, a.eps_sub,
+        a.max_inner);
+  };
+  const std::integral_constant<int, 1> one;
+  const std::integral_constant<int, 2> two;
+  if (split == 2) return go(std::true_type(), two);
+  if constexpr (DP <= 512 || sizeof(TH) == 4)
+    if (64 * Tc >= e.d) return go(std::true_type(), one);
+  if constexpr (DP <= 512) return go(std::false_type(), one);
+  return -1;  // (team_split does not lead here)
+}
+
 template <int DP>
 __device__ void run_entry(const BatchArgs& a, const BatchEntry& e, int rank, void* tile,
                           Shared& sh) {
   constexpr int DQ = DP / 4;
   constexpr int KS = DQ / 4;
   constexpr int NB = DQ / 16;
-  const int T = e.tsize, Tc = e.tcg;
   const int d = e.d;
+  // a team CG has work for one member per 64 rows of H (32 when two waves share a block):
+  // further ones would only make its barriers slower
+  const int split = a.exact && e.fac ? (DP <= 512 && e.tcg > 1 ? 1 : 0) : team_split<DP>(a, e);
+  const int T = e.tsize;
+  const int Tc = split && !a.exact ? min(e.tcg, split == 2 ? (d + 31) / 32 : (d + 63) / 64) : e.tcg;
   const int lane = lane_id(), wave = wave_id();
   const int kbase = wave * DQ;
   const EntryLayout L = entry_layout(DP, T);
@@ -1257,8 +1387,7 @@ __device__ void run_entry(const BatchArgs& a, const BatchEntry& e, int rank, voi
   // a one-workgroup CG keeps p and q in LDS (2 x DP x 16 doubles within the
   // tile region)
   const bool local_cg = Tc == 1 && 2 * (size_t)DP * KR * sizeof(double) <= kUredOffset;
-  // a larger sub-team runs the same form, each member on its share of the rows
-  const bool team_cg = Tc > 1 && 2 * (size_t)DP * KR * sizeof(double) <= kUredOffset;
+  const bool team_cg = Tc > 1 && split;
   // CG members own 16-aligned column ranges of R, Z, Q, XP and X
   const int cpw = ((d + Tc - 1) / Tc + 15) / 16 * 16;
   const int c_lo = cg ? min(d, rank * cpw) : d;
@@ -1285,6 +1414,8 @@ __device__ void run_entry(const BatchArgs& a, const BatchEntry& e, int rank, voi
     sh.step[j] = 0.0;
     sh.gnorm[j] = 0.0;
   }
+  // no tag in the words of the team CG's sums (read only after later barriers)
+  if (threadIdx.x < 2 * KR) co_store((tagged_t*)(W + L.tag) + rank * 2 * KR + threadIdx.x, 0ull);
   // x_prev = x on the owned columns
   for (int idx = threadIdx.x; idx < nown * KR; idx += kBlock) {
     const int c = c_lo + idx / KR, j = idx % KR;
@@ -1367,12 +1498,10 @@ __device__ void run_entry(const BatchArgs& a, const BatchEntry& e, int rank, voi
                     : cg_solve_local<double, DP>((const double*)e.H, e.ldh, d, R, Z, a.eps_sub,
                                                  a.max_inner);
       else if (team_cg)
-        k = a.h_f32 ? cg_solve_team<float, DP>((const float*)e.H, e.ldh, d, rank, Tc, R, Z, scal,
-                                               myscal, e.bar_cg, ep_cg, a.err, a.spin, a.eps_sub,
-                                               a.max_inner)
-                    : cg_solve_team<double, DP>((const double*)e.H, e.ldh, d, rank, Tc, R, Z,
-                                                scal, myscal, e.bar_cg, ep_cg, a.err, a.spin,
-                                                a.eps_sub, a.max_inner);
+        k = a.h_f32 ? team_solve<DP, float>(a, e, split, rank, Tc, R, Z, scal, myscal,
+                                            (tagged_t*)(W + L.tag), ep_cg)
+                    : team_solve<DP, double>(a, e, split, rank, Tc, R, Z, scal, myscal,
+                                             (tagged_t*)(W + L.tag), ep_cg);
       else
         k = a.h_f32 ? cg_solve<float, DP>((const float*)e.H, e.ldh, d, c_lo, c_hi, R, Z, Q, scal,
                                           myscal, Tc, e.bar_cg, ep_cg, a.err, a.spin, a.eps_sub,
@@ -1381,7 +1510,7 @@ __device__ void run_entry(const BatchArgs& a, const BatchEntry& e, int rank, voi
                                            scal, myscal, Tc, e.bar_cg, ep_cg, a.err, a.spin,
                                            a.eps_sub, a.max_inner);
       alive = k >= 0;
-      if (alive && Tc > 1 && !exact) ep_cg += 2u * (unsigned)k + (team_cg ? 1u : 0u);
+      if (alive && Tc > 1 && !exact) ep_cg += team_cg ? (unsigned)k + 1u : 2u * (unsigned)k;
       if (!alive) break;
       if (threadIdx.x < KR) {
         const int j = threadIdx.x;
@@ -1739,7 +1868,8 @@ size_t block_workspace_bytes(const mihs_handle* h, const BlockEntryDesc* ents, i
   int dpmax = 64;
   for (int64_t i = 0; i < count; ++i) dpmax = std::max(dpmax, dp_for(ents[i].d));
   const size_t base = block_layout(ents, count, S, G, true).total;
-  const size_t extra = (size_t)G * ((size_t)dpmax * KR + kNScal) * sizeof(double) + 256 * (size_t)count;
+  const size_t extra =
+      (size_t)G * ((size_t)dpmax * KR + kNScal + 2 * KR) * sizeof(double) + 256 * (size_t)count;
   return base + extra;
 }
 

@@ -273,4 +273,39 @@ __device__ __forceinline__ bool barrier_hier(unsigned* words, unsigned& epoch, u
   return *s_flag != 0;
 }
 
+// ---- Tagged values: data and arrival in one word ----------------------------
+// A double is handed over as two 8-byte words, each half of it beside a 32-bit tag.  The
+// reader polls the words themselves until both carry the tag it waits for (8-byte accesses
+// are single), so the hand-over costs one store and one successful load, where a barrier
+// takes a completed store, an arrival, a poll and then the load (16 workgroups, 256 values:
+// 1.7 us a round instead of 2.3).  Every value doubles in size and every reader polls all it
+// reads: 4096 values among 256 workgroups are slower than a barrier (5.1 against 4.3 us).
+//
+// A word may be rewritten (with another tag) only once every reader of the last value is
+// known to have read it; words start out with a tag that is never waited for.
+typedef unsigned long long tagged_t;  // two per double
+
+__device__ __forceinline__ void tagged_put(tagged_t* p, double v, unsigned tag) {
+  const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+  const unsigned long long t = (unsigned long long)tag << 32;
+  co_store(p, t | (b & 0xffffffffull));
+  co_store(p + 1, t | (b >> 32));
+}
+
+// Bounded: after `spin.limit` polls records a timeout in *err and returns false.
+__device__ __forceinline__ bool tagged_get(const tagged_t* p, unsigned tag, double& v, int* err,
+                                           BarrierSpin spin) {
+  for (long spins = 0;; ++spins) {
+    const tagged_t lo = co_load(p), hi = co_load(p + 1);
+    if ((unsigned)(lo >> 32) == tag && (unsigned)(hi >> 32) == tag) {
+      v = __builtin_bit_cast(double, (lo & 0xffffffffull) | (hi << 32));
+      return true;
+    }
+    if (spins > spin.limit) {
+      atomicOr(err, 1);
+      return false;
+    }
+  }
+}
+
 }  // namespace mihs

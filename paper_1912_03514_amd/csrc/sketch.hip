@@ -4,6 +4,7 @@
 // path, BF16 MFMA with FP32 accumulation for the mixed path).
 #include <math.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "gemm64.hpp"
@@ -268,14 +269,17 @@ __global__ __launch_bounds__(kBlock) void srht_stage2(const TY* __restrict__ Y, 
 // in LDS, and then adds every sampled row k = (k_hi, k_lo) with its sign:
 //     acc_k += (-1)^{popc(k_hi & i_hi)} T[k_lo],
 // so that after all blocks acc_k = ((H D A)[idx_k]) restricted to the strip.
-// Thread (c, g), c = t % 16, g = t / 16, owns column c of samples
-// g * NACC .. g * NACC + NACC - 1 in registers.  The next block's rows are
-// loaded while the current one is transformed and accumulated.  Each sample's
-// row offset in T and block index k_hi share one 32-bit word in LDS (one read
-// per sample and block; with two, the FP32 form used 236 VGPRs and the FP64
-// form spilled, against 204 and 210 now).  The partial
+// The transform's threads (c, g), c = t % 16, g = t / 16, hold column c of R rows; the
+// accumulation's threads own the 16 bytes of columns from VC (t % (16 / VC)) of NS samples,
+// in registers, so that one LDS read of T, one of the sample's word (its row offset in T and
+// block index k_hi) and one sign serve VC = 4 (FP32) or 2 (FP64) columns.  The next block's
+// rows are loaded while the current one is transformed and accumulated.  The partial
 // sums of the workgroup's block range go to P[part] (or, with one range per
 // strip, scaled straight to SA).
+//
+// Bound: compute and LDS latency of the accumulation and the transform (two waves per SIMD;
+// the loads have a whole block's time to land).  One column per thread took 8.0 us a
+// 1024-row block of FP64 A with 2048 samples; see launch_srht_fused for the present rate.
 // ---------------------------------------------------------------------------
 // Mixed CountSketch -> Gaussian: the FP32 bucket sums CA enter the Gaussian
 // stage as three BF16 terms (hi + mid + lo), so that the BF16 products keep
@@ -287,7 +291,14 @@ constexpr int kFusedThreads = 512;
 constexpr int kBufferRsrcWord3 = 0x00020000;  // raw 32-bit buffer data (gfx9 family)
 constexpr int kBufferNt = 2;                  // cache policy: non-temporal
 constexpr int kFusedW = 16;       // columns per strip
-constexpr int kFusedLdt = kFusedW + 1;
+// columns per accumulating thread (16 bytes) and LDS row stride of T (16-byte rows)
+template <typename TY>
+constexpr int fused_vc() { return 16 / (int)sizeof(TY); }
+template <typename TY>
+constexpr int fused_ldt() { return kFusedW + fused_vc<TY>(); }
+// threads that share a sample set
+template <typename TY>
+constexpr int fused_groups() { return kFusedThreads * fused_vc<TY>() / kFusedW; }
 
 // sign words: bit j of word w is set iff D_{32 w + j} = -1
 __global__ void srht_sign_words_kernel(uint32_t* words, int64_t nwords, uint32_t seed) {
@@ -299,7 +310,7 @@ __global__ void srht_sign_words_kernel(uint32_t* words, int64_t nwords, uint32_t
   words[w] = v;
 }
 
-template <typename TA, typename TY, int LOGB, int NACC, typename TS>
+template <typename TA, typename TY, int LOGB, int NS, typename TS>
 __global__ __launch_bounds__(kFusedThreads) void srht_fused_kernel(
     const TA* __restrict__ A, int64_t lda, int64_t d, const uint32_t* __restrict__ signw,
     const int* __restrict__ idx, int64_t m, int64_t nblk, int nparts, TY* __restrict__ P,
@@ -307,27 +318,29 @@ __global__ __launch_bounds__(kFusedThreads) void srht_fused_kernel(
   constexpr int B = 1 << LOGB;
   constexpr int R = B * kFusedW / kFusedThreads;  // rows per thread per phase (16 or 32)
   static_assert(R == 16 || R == 32, "block shape");
+  constexpr int VC = fused_vc<TY>(), LDT = fused_ldt<TY>(), GS = fused_groups<TY>();
+  typedef TY vec_t __attribute__((ext_vector_type(VC)));
   extern __shared__ unsigned char smem_raw[];
-  TY* T = (TY*)smem_raw;                                   // B x kFusedLdt
-  // per sample: its row offset in T (low 16 bits) and k_hi (high 16 bits), one
-  // LDS read per sample and block
-  uint32_t* s_smp = (uint32_t*)(T + (size_t)B * kFusedLdt);  // 32 * NACC
+  TY* T = (TY*)smem_raw;  // B x LDT
+  // per sample: its row offset in T (low 16 bits) and k_hi (high 16 bits)
+  uint32_t* s_smp = (uint32_t*)(T + (size_t)B * LDT);      // GS * NS
   const int t = threadIdx.x;
   const int c = t % kFusedW, g = t / kFusedW;              // g in [0, 32)
+  const int cs = VC * (t % (kFusedW / VC)), gs = t / (kFusedW / VC);  // accumulation
   const int strip = blockIdx.x % (int)((d + kFusedW - 1) / kFusedW);
   const int part = blockIdx.x / (int)((d + kFusedW - 1) / kFusedW);
   const int64_t col = (int64_t)strip * kFusedW + c;
   const bool col_ok = col < d;
   const int64_t b0 = nblk * part / nparts, b1 = nblk * (part + 1) / nparts;
 
-  for (int k = t; k < 32 * NACC; k += kFusedThreads) {
+  for (int k = t; k < GS * NS; k += kFusedThreads) {
     const int v = k < m ? idx[k] : 0;
     const uint32_t khi = k < m ? (uint32_t)(v >> LOGB) : 0u;
-    s_smp[k] = (uint32_t)((v & (B - 1)) * kFusedLdt) | (khi << 16);
+    s_smp[k] = (uint32_t)((v & (B - 1)) * LDT) | (khi << 16);
   }
-  TY acc[NACC];
+  vec_t acc[NS];
 #pragma unroll
-  for (int j = 0; j < NACC; ++j) acc[j] = TY(0);
+  for (int j = 0; j < NS; ++j) acc[j] = (vec_t)(TY(0));
 
   // rows g + 32 i of block b, this thread's column, as buffer loads: the
   // block's base in a buffer resource, row 32 i's byte offset in a scalar
@@ -367,13 +380,13 @@ __global__ __launch_bounds__(kFusedThreads) void srht_fused_kernel(
     fwht_regs<TY, R>(x);
     __syncthreads();  // the previous block's accumulation has read T
 #pragma unroll
-    for (int i = 0; i < R; ++i) T[(g + 32 * i) * kFusedLdt + c] = x[i];
+    for (int i = 0; i < R; ++i) T[(g + 32 * i) * LDT + c] = x[i];
     __syncthreads();
     // phase 2: the butterflies of row bits 0 .. log2(R)-1 on rows R g + i
     {
       TY y[R];
 #pragma unroll
-      for (int i = 0; i < R; ++i) y[i] = T[(R * g + i) * kFusedLdt + c];
+      for (int i = 0; i < R; ++i) y[i] = T[(R * g + i) * LDT + c];
       fwht_regs<TY, R>(y);
       if constexpr (R == 16) {
         // row bit 4: rows 16 g + i and 16 (g ^ 1) + i live in threads t and t ^ 16
@@ -386,40 +399,43 @@ __global__ __launch_bounds__(kFusedThreads) void srht_fused_kernel(
         }
       }
 #pragma unroll
-      for (int i = 0; i < R; ++i) T[(R * g + i) * kFusedLdt + c] = y[i];
+      for (int i = 0; i < R; ++i) T[(R * g + i) * LDT + c] = y[i];
     }
     __syncthreads();
-    // every owned sample: acc_k += (-1)^{popc(k_hi & b)} T[k_lo][c], eight
+    // every owned sample: acc_k += (-1)^{popc(k_hi & b)} T[k_lo][cs ..], four
     // samples at a time (the empty asm keeps the compiler from hoisting every
     // sample's LDS reads at once, which would not fit in the registers)
     const uint32_t bb = (uint32_t)b;
-    const TY* Tc = T + c;
+    const TY* Tc = T + cs;
+    const uint32_t* smp = s_smp + gs * NS;
 #pragma unroll
-    for (int j0 = 0; j0 < NACC; j0 += 8) {
+    for (int j0 = 0; j0 < NS; j0 += 4) {
       asm volatile("" ::: "memory");
+      uint32_t w[4];
 #pragma unroll
-      for (int j = j0; j < j0 + 8; ++j) {
-        const int k = g * NACC + j;
-        const uint32_t smp = s_smp[k];
-        const TY v = Tc[smp & 0xFFFFu];
-        const bool neg = (__popc((smp >> 16) & bb) & 1) != 0;
-        acc[j] += neg ? -v : v;
+      for (int j = 0; j < 4; ++j) w[j] = smp[j0 + j];
+      vec_t v[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[j] = *(const vec_t*)(Tc + (w[j] & 0xFFFFu));
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const bool neg = (__popc((w[j] >> 16) & bb) & 1) != 0;
+#pragma unroll
+        for (int q = 0; q < VC; ++q) acc[j0 + j][q] += neg ? -v[j][q] : v[j][q];
       }
     }
   }
-  if (!col_ok) return;
-  if (nparts == 1) {
+  TY* Pp = nparts == 1 ? nullptr : P + (int64_t)part * m * ldp;
 #pragma unroll
-    for (int j = 0; j < NACC; ++j) {
-      const int64_t k = (int64_t)g * NACC + j;
-      if (k < m) SA[k * ldsa + col] = (TS)((double)acc[j] * scale);
-    }
-  } else {
-    TY* Pp = P + (int64_t)part * m * ldp;
+  for (int j = 0; j < NS; ++j) {
+    const int64_t k = (int64_t)gs * NS + j;
 #pragma unroll
-    for (int j = 0; j < NACC; ++j) {
-      const int64_t k = (int64_t)g * NACC + j;
-      if (k < m) Pp[k * ldp + col] = acc[j];
+    for (int q = 0; q < VC; ++q) {
+      const int64_t cq = (int64_t)strip * kFusedW + cs + q;
+      if (k < m && cq < d) {
+        if (Pp) Pp[k * ldp + cq] = acc[j][q];
+        else SA[k * ldsa + cq] = (TS)((double)acc[j][q] * scale);
+      }
     }
   }
 }
@@ -1065,11 +1081,11 @@ int srht_logB(int64_t n) {
 }
 
 // The one-read SRHT: block size (B = 2^logb rows), samples per thread, and the
-// number of block ranges per strip (enough workgroups for one per CU).  Used
-// when n >= B and m <= 2048; else the two-stage transform below.
+// number of block ranges per strip.  Used when n >= B and the samples fit the registers
+// (m <= 4096 in FP32, 2048 in FP64); else the two-stage transform below.
 struct SrhtFusedPlan {
   bool ok = false;
-  int logb = 0, nacc = 0, nparts = 1;
+  int logb = 0, ns = 0, nparts = 1;
   int64_t nblk = 0, strips = 0;
   size_t idx_bytes = 0, sign_bytes = 0, part_bytes = 0, lds = 0;
   size_t total() const { return idx_bytes + sign_bytes + part_bytes; }
@@ -1077,22 +1093,37 @@ struct SrhtFusedPlan {
 
 SrhtFusedPlan srht_fused_plan(const mihs_handle* h, int64_t n, int64_t d, int64_t m, int ty_bytes) {
   SrhtFusedPlan F;
-  F.logb = ty_bytes == 4 ? 10 : 9;
-  if (n < (1LL << F.logb) || (n & (n - 1)) != 0 || m > 2048 || m < 1) return F;
+  const bool f32 = ty_bytes == 4;
+  F.logb = f32 ? 10 : 9;
+  if (n < (1LL << F.logb) || (n & (n - 1)) != 0 || m > (f32 ? 4096 : 2048) || m < 1) return F;
   // a sample's block index k_hi is kept in 16 bits
   if ((n >> F.logb) > 65536) return F;
   F.ok = true;
-  F.nacc = m <= 512 ? 16 : (m <= 1024 ? 32 : 64);
+  const int groups = f32 ? fused_groups<float>() : fused_groups<double>();
+  F.ns = m <= 512 ? 512 / groups : m <= 1024 ? 1024 / groups : m <= 2048 ? 2048 / groups
+                                             : m <= 3072 ? 3072 / groups : 4096 / groups;
   F.nblk = n >> F.logb;
   F.strips = (d + kFusedW - 1) / kFusedW;
-  int64_t parts = (h->num_cu + F.strips - 1) / F.strips;
-  if (parts > F.nblk) parts = F.nblk;
-  if (parts < 1) parts = 1;
-  F.nparts = (int)parts;
+  // Block ranges per strip: one workgroup runs per CU, so strips x ranges workgroups take
+  // ceil(that / CUs) rounds of nblk / ranges blocks, and every range writes and reads back
+  // its partial sums.  The least of rounds x blocks x ~3 us (a 1024-row FP32 block; twice
+  // that from FP64 rows) plus the partials' bytes at ~4 TB/s.
+  double best = 0.0;
+  const int64_t pmax = std::max<int64_t>(32, 2 * ceil_div(h->num_cu, F.strips));
+  for (int64_t p = 1; p <= pmax && p <= F.nblk; ++p) {
+    const double rounds = (double)ceil_div(F.strips * p, h->num_cu);
+    const double us = rounds * (double)ceil_div(F.nblk, p) * 3.0 +
+                      (p > 1 ? 2.0 * (double)p * (double)m * (double)d * ty_bytes / 4e6 : 0.0);
+    if (p == 1 || us < best) {
+      best = us;
+      F.nparts = (int)p;
+    }
+  }
   F.idx_bytes = align_up((size_t)m * 4, 256);
   F.sign_bytes = align_up((size_t)(n / 32) * 4, 256);
   F.part_bytes = F.nparts > 1 ? align_up((size_t)F.nparts * m * d * ty_bytes, 256) : 0;
-  F.lds = (size_t)(1 << F.logb) * kFusedLdt * ty_bytes + 32 * (size_t)F.nacc * 4;
+  F.lds = (size_t)(1 << F.logb) * (f32 ? fused_ldt<float>() : fused_ldt<double>()) * ty_bytes +
+          (size_t)groups * F.ns * 4;
   return F;
 }
 
@@ -1109,10 +1140,22 @@ int launch_srht_fused(const SrhtFusedPlan& F, const TA* A, int64_t lda, int64_t 
                        F.nblk, F.nparts, P, d, SA, ldsa, scale);
     return MIHS_OK;
   };
-  int rc;
-  if (F.nacc == 16) rc = go(srht_fused_kernel<TA, TY, LOGB, 16, TS>);
-  else if (F.nacc == 32) rc = go(srht_fused_kernel<TA, TY, LOGB, 32, TS>);
-  else rc = go(srht_fused_kernel<TA, TY, LOGB, 64, TS>);
+  int rc = MIHS_ERR_UNSUPPORTED;
+  if constexpr (sizeof(TY) == 4) {
+    switch (F.ns) {
+      case 4: rc = go(srht_fused_kernel<TA, TY, LOGB, 4, TS>); break;
+      case 8: rc = go(srht_fused_kernel<TA, TY, LOGB, 8, TS>); break;
+      case 16: rc = go(srht_fused_kernel<TA, TY, LOGB, 16, TS>); break;
+      case 24: rc = go(srht_fused_kernel<TA, TY, LOGB, 24, TS>); break;
+      case 32: rc = go(srht_fused_kernel<TA, TY, LOGB, 32, TS>); break;
+    }
+  } else {
+    switch (F.ns) {
+      case 8: rc = go(srht_fused_kernel<TA, TY, LOGB, 8, TS>); break;
+      case 16: rc = go(srht_fused_kernel<TA, TY, LOGB, 16, TS>); break;
+      case 32: rc = go(srht_fused_kernel<TA, TY, LOGB, 32, TS>); break;
+    }
+  }
   if (rc) return rc;
   if (F.nparts > 1)
     hipLaunchKernelGGL((srht_parts_sum_kernel<TY, TS>), dim3((unsigned)ceil_div(m * d, 256)),

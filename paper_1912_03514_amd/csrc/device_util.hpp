@@ -73,6 +73,18 @@ __device__ __forceinline__ T block_sum(T v, T* scratch) {
   return t;
 }
 
+// Workgroup barrier without the memory fence of __syncthreads, whose release
+// would wait for every load in flight (rows fetched ahead).
+// The caller waits for its own LDS writes first (lgkmcnt(0)); the empty asm
+// statements keep the compiler from moving memory accesses across it.
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
 // Sum of `count` doubles at base[0], base[stride], ... in a fixed order.
 template <typename T>
 __device__ __forceinline__ double block_sum_strided(const T* base, int count, int64_t stride,

@@ -277,9 +277,11 @@ __global__ __launch_bounds__(kBlock) void srht_stage2(const TY* __restrict__ Y, 
 // sums of the workgroup's block range go to P[part] (or, with one range per
 // strip, scaled straight to SA).
 //
-// Bound: compute and LDS latency of the accumulation and the transform (two waves per SIMD;
-// the loads have a whole block's time to land).  One column per thread took 8.0 us a
-// 1024-row block of FP64 A with 2048 samples; see launch_srht_fused for the present rate.
+// Bound: the 128-byte row segments' rate from memory and, with many samples, the LDS reads
+// and arithmetic of the accumulation (two waves per SIMD).  2^18 x 2048 FP64, m = 2048 in FP32:
+// 1065 us with one column per accumulating thread, 880 us now (4.9 TB/s); 2^16 x 4096,
+// m = 4096: 555 us (1430 in two stages); 2^17 x 1500 FP32, m = 3000: 1003 us in two stages,
+// 420 before neighbouring strips shared an L2, 341 now.
 // ---------------------------------------------------------------------------
 // Mixed CountSketch -> Gaussian: the FP32 bucket sums CA enter the Gaussian
 // stage as three BF16 terms (hi + mid + lo), so that the BF16 products keep
@@ -291,14 +293,35 @@ constexpr int kFusedThreads = 512;
 constexpr int kBufferRsrcWord3 = 0x00020000;  // raw 32-bit buffer data (gfx9 family)
 constexpr int kBufferNt = 2;                  // cache policy: non-temporal
 constexpr int kFusedW = 16;       // columns per strip
-// columns per accumulating thread (16 bytes) and LDS row stride of T (16-byte rows)
+// columns per accumulating thread (16 bytes)
 template <typename TY>
 constexpr int fused_vc() { return 16 / (int)sizeof(TY); }
-template <typename TY>
-constexpr int fused_ldt() { return kFusedW + fused_vc<TY>(); }
+// Rows of T lie one after the other in LDS with an unused one after every R (R rows per
+// thread and phase): both the rows g, g + 1, .. that a wave's first phase stores together and
+// the rows R g, R (g + 1), .. of its second phase then fall into different banks.
+MIHS_HOST_DEVICE constexpr int fused_row(int r, int R) { return r + r / R; }
 // threads that share a sample set
 template <typename TY>
 constexpr int fused_groups() { return kFusedThreads * fused_vc<TY>() / kFusedW; }
+
+// Strip and block range of a workgroup.  A strip's 16 columns of FP32 rows are half a
+// 128-byte line, so two neighbouring strips of the same range go to workgroups 8 apart:
+// dispatched together to the same XCD, they share the lines in its L2 (apart, every line came
+// from memory twice).
+template <typename TA>
+constexpr int fused_pair() { return sizeof(TA) == 4 ? 2 : 1; }
+template <typename TA>
+__device__ __forceinline__ bool fused_place(int strips, int nparts, int& strip, int& part) {
+  int b = blockIdx.x, sub = 0, n = strips;
+  if (fused_pair<TA>() == 2) {
+    sub = b / kXcds % 2;
+    b = b / (2 * kXcds) * kXcds + b % kXcds;
+    n = (strips + 1) / 2;
+  }
+  strip = b % n * fused_pair<TA>() + sub;
+  part = b / n;
+  return strip < strips && part < nparts;
+}
 
 // sign words: bit j of word w is set iff D_{32 w + j} = -1
 __global__ void srht_sign_words_kernel(uint32_t* words, int64_t nwords, uint32_t seed) {
@@ -318,17 +341,17 @@ __global__ __launch_bounds__(kFusedThreads) void srht_fused_kernel(
   constexpr int B = 1 << LOGB;
   constexpr int R = B * kFusedW / kFusedThreads;  // rows per thread per phase (16 or 32)
   static_assert(R == 16 || R == 32, "block shape");
-  constexpr int VC = fused_vc<TY>(), LDT = fused_ldt<TY>(), GS = fused_groups<TY>();
+  constexpr int VC = fused_vc<TY>(), GS = fused_groups<TY>();
   typedef TY vec_t __attribute__((ext_vector_type(VC)));
   extern __shared__ unsigned char smem_raw[];
-  TY* T = (TY*)smem_raw;  // B x LDT
-  // per sample: its row offset in T (low 16 bits) and k_hi (high 16 bits)
-  uint32_t* s_smp = (uint32_t*)(T + (size_t)B * LDT);      // GS * NS
+  TY* T = (TY*)smem_raw;  // fused_row(B) x kFusedW
+  // per sample: k_hi (low 16 bits) and its row's offset in T in 16-byte units (high 16)
+  uint32_t* s_smp = (uint32_t*)(T + (size_t)fused_row(B, R) * kFusedW);      // GS * NS
   const int t = threadIdx.x;
   const int c = t % kFusedW, g = t / kFusedW;              // g in [0, 32)
   const int cs = VC * (t % (kFusedW / VC)), gs = t / (kFusedW / VC);  // accumulation
-  const int strip = blockIdx.x % (int)((d + kFusedW - 1) / kFusedW);
-  const int part = blockIdx.x / (int)((d + kFusedW - 1) / kFusedW);
+  int strip, part;
+  if (!fused_place<TA>((int)((d + kFusedW - 1) / kFusedW), nparts, strip, part)) return;
   const int64_t col = (int64_t)strip * kFusedW + c;
   const bool col_ok = col < d;
   const int64_t b0 = nblk * part / nparts, b1 = nblk * (part + 1) / nparts;
@@ -336,7 +359,7 @@ __global__ __launch_bounds__(kFusedThreads) void srht_fused_kernel(
   for (int k = t; k < GS * NS; k += kFusedThreads) {
     const int v = k < m ? idx[k] : 0;
     const uint32_t khi = k < m ? (uint32_t)(v >> LOGB) : 0u;
-    s_smp[k] = (uint32_t)((v & (B - 1)) * LDT) | (khi << 16);
+    s_smp[k] = (uint32_t)(fused_row(v & (B - 1), R) * (kFusedW / VC)) << 16 | khi;
   }
   vec_t acc[NS];
 #pragma unroll
@@ -345,7 +368,8 @@ __global__ __launch_bounds__(kFusedThreads) void srht_fused_kernel(
   // rows g + 32 i of block b, this thread's column, as buffer loads: the
   // block's base in a buffer resource, row 32 i's byte offset in a scalar
   // register and one per-lane byte offset, so that the row addresses do not
-  // each occupy a pair of vector registers.  Non-temporal: A is read once.
+  // each occupy a pair of vector registers.  Non-temporal for FP64 (each line is
+  // read once; two strips share one of FP32).
   // Every offset stays below the block's B rows (checked against num_records).
   TA xa[R];
   const uint32_t lane_off = (uint32_t)(((int64_t)g * lda + (col_ok ? col : 0)) * sizeof(TA));
@@ -360,7 +384,7 @@ __global__ __launch_bounds__(kFusedThreads) void srht_fused_kernel(
         const auto v = __builtin_amdgcn_raw_buffer_load_b64(rs, lane_off, i * row32, kBufferNt);
         xa[i] = __builtin_bit_cast(TA, v);
       } else {
-        const auto v = __builtin_amdgcn_raw_buffer_load_b32(rs, lane_off, i * row32, kBufferNt);
+        const auto v = __builtin_amdgcn_raw_buffer_load_b32(rs, lane_off, i * row32, 0);
         xa[i] = __builtin_bit_cast(TA, v);
       }
     }
@@ -375,18 +399,20 @@ __global__ __launch_bounds__(kFusedThreads) void srht_fused_kernel(
       const bool neg = (sw[i] >> g) & 1u;
       x[i] = neg ? -(TY)xa[i] : (TY)xa[i];
     }
-    // the next block's rows as soon as this block's are in x
-    if (b + 1 < b1) load_block(b + 1);
+    // the next block's rows as soon as this block's are in x, or (FP64 rows beside 96 and
+    // more accumulators: the registers would spill) once the transform is done
+    constexpr bool kLate = sizeof(TA) == 8 && sizeof(TY) == 4 && NS >= 24;
+    if (!kLate && b + 1 < b1) load_block(b + 1);
     fwht_regs<TY, R>(x);
-    __syncthreads();  // the previous block's accumulation has read T
+    lds_barrier();  // the previous block's accumulation has read T
 #pragma unroll
-    for (int i = 0; i < R; ++i) T[(g + 32 * i) * LDT + c] = x[i];
-    __syncthreads();
+    for (int i = 0; i < R; ++i) T[fused_row(g + 32 * i, R) * kFusedW + c] = x[i];
+    lds_barrier();
     // phase 2: the butterflies of row bits 0 .. log2(R)-1 on rows R g + i
     {
       TY y[R];
 #pragma unroll
-      for (int i = 0; i < R; ++i) y[i] = T[(R * g + i) * LDT + c];
+      for (int i = 0; i < R; ++i) y[i] = T[((R + 1) * g + i) * kFusedW + c];
       fwht_regs<TY, R>(y);
       if constexpr (R == 16) {
         // row bit 4: rows 16 g + i and 16 (g ^ 1) + i live in threads t and t ^ 16
@@ -399,29 +425,42 @@ __global__ __launch_bounds__(kFusedThreads) void srht_fused_kernel(
         }
       }
 #pragma unroll
-      for (int i = 0; i < R; ++i) T[(R * g + i) * LDT + c] = y[i];
+      for (int i = 0; i < R; ++i) T[((R + 1) * g + i) * kFusedW + c] = y[i];
     }
-    __syncthreads();
-    // every owned sample: acc_k += (-1)^{popc(k_hi & b)} T[k_lo][cs ..], four
-    // samples at a time (the empty asm keeps the compiler from hoisting every
-    // sample's LDS reads at once, which would not fit in the registers)
+    if (kLate && b + 1 < b1) load_block(b + 1);
+    lds_barrier();
+    // every owned sample: acc_k += (-1)^{popc(k_hi & b)} T[k_lo][cs ..], NG samples
+    // at a time (the empty asm keeps the compiler from hoisting every sample's LDS
+    // reads at once, which would not fit in the registers).  The sign enters as a
+    // factor of exactly +-1, one instruction per column.
+    constexpr int NG = NS % 8 == 0 && (NS < 32 || sizeof(TA) == 4) ? 8 : 4;
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     const uint32_t bb = (uint32_t)b;
-    const TY* Tc = T + cs;
+    const char* Tc = (const char*)(T + cs);
     const uint32_t* smp = s_smp + gs * NS;
 #pragma unroll
-    for (int j0 = 0; j0 < NS; j0 += 4) {
+    for (int j0 = 0; j0 < NS; j0 += NG) {
       asm volatile("" ::: "memory");
-      uint32_t w[4];
+      uint32_t w[NG];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) w[j] = smp[j0 + j];
-      vec_t v[4];
+      for (int j = 0; j < NG; j += 4) {
+        const u32x4 x = *(const u32x4*)(smp + j0 + j);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) v[j] = *(const vec_t*)(Tc + (w[j] & 0xFFFFu));
+        for (int i = 0; i < 4; ++i) w[j + i] = x[i];
+      }
+      vec_t v[NG];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const bool neg = (__popc((w[j] >> 16) & bb) & 1) != 0;
+      for (int j = 0; j < NG; ++j) v[j] = *(const vec_t*)(Tc + ((w[j] >> 12) & ~15u));
 #pragma unroll
-        for (int q = 0; q < VC; ++q) acc[j0 + j][q] += neg ? -v[j][q] : v[j][q];
+      for (int j = 0; j < NG; ++j) {
+        const uint32_t neg = (uint32_t)__popc(w[j] & bb) << 31;  // b < 2^16
+        TY sgn;
+        if constexpr (sizeof(TY) == 4)
+          sgn = __uint_as_float(0x3F800000u | neg);
+        else
+          sgn = __hiloint2double((int)(0x3FF00000u | neg), 0);
+#pragma unroll
+        for (int q = 0; q < VC; ++q) acc[j0 + j][q] += v[j][q] * sgn;
       }
     }
   }
@@ -1122,7 +1161,7 @@ SrhtFusedPlan srht_fused_plan(const mihs_handle* h, int64_t n, int64_t d, int64_
   F.idx_bytes = align_up((size_t)m * 4, 256);
   F.sign_bytes = align_up((size_t)(n / 32) * 4, 256);
   F.part_bytes = F.nparts > 1 ? align_up((size_t)F.nparts * m * d * ty_bytes, 256) : 0;
-  F.lds = (size_t)(1 << F.logb) * (f32 ? fused_ldt<float>() : fused_ldt<double>()) * ty_bytes +
+  F.lds = (size_t)fused_row(1 << F.logb, f32 ? 32 : 16) * kFusedW * ty_bytes +
           (size_t)groups * F.ns * 4;
   return F;
 }
@@ -1131,7 +1170,10 @@ template <typename TA, typename TY, int LOGB, typename TS>
 int launch_srht_fused(const SrhtFusedPlan& F, const TA* A, int64_t lda, int64_t d, int64_t m,
                       const uint32_t* signw, const int* idx, TY* P, TS* SA, int64_t ldsa,
                       double scale, hipStream_t st) {
-  const dim3 grid((unsigned)(F.strips * F.nparts));
+  int64_t wgs = F.strips * F.nparts;
+  if (fused_pair<TA>() == 2)
+    wgs = ceil_div((F.strips + 1) / 2 * F.nparts, kXcds) * 2 * kXcds;
+  const dim3 grid((unsigned)wgs);
   auto go = [&](auto kern) -> int {
     if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)F.lds) != hipSuccess)

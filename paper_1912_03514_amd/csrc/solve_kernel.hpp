@@ -146,17 +146,6 @@ __device__ __forceinline__ void rowpass(const TM* __restrict__ M, int64_t ld, in
   }
 }
 
-// Workgroup barrier without the memory fence of __syncthreads, whose release
-// would wait for every load in flight (here: the next rows, fetched ahead).
-// The caller waits for its own LDS writes first (lgkmcnt(0)); the empty asm
-// statements keep the compiler from moving memory accesses across it.
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
-
 // The gradient pass for rows too long for one wave's registers (d > 2048): the
 // four waves split every row into quarters of 64 * EQ columns, each lane holding
 // EQ entries of its wave's quarter.  Per group of R rows every wave forms its

@@ -59,6 +59,16 @@ __device__ __forceinline__ T wave_sum(T v) {
   return (read_lane(v, 0) + read_lane(v, 16)) + (read_lane(v, 32) + read_lane(v, 48));
 }
 
+// Sum over each row of 16 lanes, to its lanes.
+template <typename T>
+__device__ __forceinline__ T row16_sum(T v) {
+  v += dpp_row_move<0xB1>(v);
+  v += dpp_row_move<0x4E>(v);
+  v += dpp_row_move<0x141>(v);
+  v += dpp_row_move<0x140>(v);
+  return v;
+}
+
 // Deterministic workgroup sum (256 threads); every thread receives the total.
 // `scratch` is __shared__ storage of at least kWavesPerBlock elements.
 template <typename T>
@@ -304,20 +314,42 @@ __device__ __forceinline__ void tagged_put(tagged_t* p, double v, unsigned tag) 
   co_store(p + 1, t | (b >> 32));
 }
 
-// Bounded: after `spin.limit` polls records a timeout in *err and returns false.
-__device__ __forceinline__ bool tagged_get(const tagged_t* p, unsigned tag, double& v, int* err,
+// Values of several words (those that are `on`), all polled together.  Bounded: after
+// `spin.limit` polls records a timeout in *err and returns false.
+template <int N>
+__device__ __forceinline__ bool tagged_get(const tagged_t* const (&p)[N], const bool (&on)[N],
+                                           unsigned tag, double (&v)[N], int* err,
                                            BarrierSpin spin) {
+  tagged_t lo[N], hi[N];
   for (long spins = 0;; ++spins) {
-    const tagged_t lo = co_load(p), hi = co_load(p + 1);
-    if ((unsigned)(lo >> 32) == tag && (unsigned)(hi >> 32) == tag) {
-      v = __builtin_bit_cast(double, (lo & 0xffffffffull) | (hi << 32));
-      return true;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      lo[i] = on[i] ? co_load(p[i]) : (tagged_t)tag << 32;
+      hi[i] = on[i] ? co_load(p[i] + 1) : (tagged_t)tag << 32;
     }
+    bool ready = true;
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+      ready = ready && (unsigned)(lo[i] >> 32) == tag && (unsigned)(hi[i] >> 32) == tag;
+    if (ready) break;
     if (spins > spin.limit) {
       atomicOr(err, 1);
       return false;
     }
   }
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+    v[i] = __builtin_bit_cast(double, (lo[i] & 0xffffffffull) | (hi[i] << 32));
+  return true;
+}
+__device__ __forceinline__ bool tagged_get(const tagged_t* p, unsigned tag, double& v, int* err,
+                                           BarrierSpin spin) {
+  const tagged_t* const q[1] = {p};
+  const bool on[1] = {true};
+  double x[1];
+  const bool ok = tagged_get<1>(q, on, tag, x, err, spin);
+  if (ok) v = x[0];
+  return ok;
 }
 
 }  // namespace mihs

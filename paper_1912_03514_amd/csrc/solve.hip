@@ -110,7 +110,8 @@ int launch_grad_partial_ept(int ept, int G, size_t shmem, hipStream_t stream, co
 }
 
 __global__ void zero_words(unsigned* p, int count) {
-  for (int i = threadIdx.x; i < count; i += blockDim.x) p[i] = 0u;
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < count; i += gridDim.x * blockDim.x)
+    p[i] = 0u;
 }
 
 // Mixed precision stores the inner solver's operator (SA, or its Gram matrix)
@@ -130,7 +131,7 @@ SolveKernel pick_kernel(int a_f32, int mixed, int ept, bool gram, bool res) {
 bool use_gram(int64_t m, int64_t d) { return m >= d; }
 
 struct SolveLayout {
-  size_t partA, partS, scal, vecs, xp, bar, gram, yrow, total;
+  size_t partA, partS, scal, vecs, xp, bar, tags, tagw, gram, yrow, total;
 };
 
 // Barrier region: line 0 = top counter of the all-workgroup barrier, lines 1-8
@@ -138,6 +139,11 @@ struct SolveLayout {
 // line 11 = status word, lines 12-20 = top and group counters of the two-level
 // inner-solve barrier (128-byte lines).
 constexpr size_t kBarLines = 21;
+
+// The CG's vector travels as tagged values up to this many columns, by barrier above: every
+// workgroup polls all of it at twice its size (256 workgroups, a round of 2048 values: 3.4 us
+// tagged, 3.9 by barrier; of 4096: 5.1 against 4.3).
+constexpr int64_t kTagCols = 2048;
 
 // gram_bytes: size of the Gram matrix region (0 when the CG streams SA).
 SolveLayout layout(int G, int Gc, int64_t dpad, size_t gram_bytes, int64_t m) {
@@ -149,6 +155,10 @@ SolveLayout layout(int G, int Gc, int64_t dpad, size_t gram_bytes, int64_t m) {
   L.vecs = off;  off = align_up(off + 4 * (size_t)dpad * 8, 256);
   L.xp = off;    off = align_up(off + (size_t)dpad * 8, 256);
   L.bar = off;   off = align_up(off + kBarLines * 128, 256);
+  // tagged scalars and vector entries, cleared with the barrier words by every launch
+  L.tags = off;  off += 2 * (size_t)Gc * 2 * 16;
+  L.tagw = off;  off += dpad <= kTagCols ? 2 * (size_t)dpad * 16 : 0;
+  off = align_up(off, 256);
   L.gram = off;  off = align_up(off + gram_bytes, 256);
   L.yrow = off;  off = align_up(off + (size_t)m * 8, 256);
   L.total = off;
@@ -340,6 +350,8 @@ int launch_solve(const mihs_handle* h, const SolveDesc& s, void* ws, size_t ws_b
   a.G = G;
   a.Gc = Gc;
   a.cpw = cpw;
+  a.tags = (tagged_t*)(base + L.tags);
+  a.tagw = dpad <= kTagCols ? (tagged_t*)(base + L.tagw) : nullptr;
   a.spin_fast.limit = 1L << 26;  // ~64-clock polls: a few seconds at most
   a.spin_fast.sleep = 1;
   a.spin_idle.limit = 1L << 24;  // ~1000-clock polls while the inner solve runs
@@ -361,7 +373,10 @@ int launch_solve(const mihs_handle* h, const SolveDesc& s, void* ws, size_t ws_b
     if (rc) return rc;
   }
 
-  hipLaunchKernelGGL(zero_words, dim3(1), dim3(256), 0, stream, bar, (int)(kBarLines * 32));
+  // barrier words and tags (contiguous up to the Gram matrix; the tags only where used)
+  const int zwords = (int)(((gram ? L.gram : L.tags) - L.bar) / 4);
+  hipLaunchKernelGGL(zero_words, dim3((unsigned)((zwords + 1023) / 1024)), dim3(256), 0, stream,
+                     bar, zwords);
   if (hipGetLastError() != hipSuccess) return MIHS_ERR_HIP;
   void* args[] = {&a};
   if (hipLaunchCooperativeKernel((const void*)kern, dim3(G), dim3(kBlock), args, shmem, stream) !=

@@ -84,6 +84,8 @@ struct SolveArgs {
   int d, dpad, G, Gc, cpw;
   int cg_hier;        // inner-solve group large enough for the two-level barrier
   int32_t xw[kXcds];  // gradient-pass row weight of each XCD (row_split_bound)
+  tagged_t* tagw;     // 2 x dpad tagged vector entries (null: the vector goes by barrier)
+  tagged_t* tags;     // 2 x Gc x 2 tagged scalars
   BarrierSpin spin_fast, spin_idle;
 };
 
@@ -568,6 +570,8 @@ __global__ __launch_bounds__(kBlock) void solve_kernel(SolveArgs a) {
   __shared__ double s_part[2 * kQuarterRows * kWavesPerBlock];  // rowpass_quarters exchange
   constexpr int EQ = EPT >= 4 ? EPT / 4 : 1;
   constexpr int NR = resident_rows<TS, EQ>();
+  // tagged exchanges (d <= 2048, owned rows in registers)
+  constexpr bool TAGGED = GRAM && RES && EPT < 64;
   __shared__ double s_res[kResParts * NR];  // resident rows' partial products
   __shared__ double s_u[NR], s_y[NR];       // SA rows: u of this step, y of the last one
   __shared__ int s_flag;
@@ -576,7 +580,7 @@ __global__ __launch_bounds__(kBlock) void solve_kernel(SolveArgs a) {
   const int G = a.G, Gc = a.Gc;
   const int d = a.d;
   const bool in_cg = w < Gc;
-  unsigned ep_all = 0, ep_cg = 0;
+  unsigned ep_all = 0, ep_cg = 0, tag = 0;
   const int c_lo = in_cg ? min(d, w * cpw) : d;
   const int c_hi = in_cg ? min(d, c_lo + cpw) : d;
   const int nown = c_hi - c_lo;
@@ -714,10 +718,10 @@ __global__ __launch_bounds__(kBlock) void solve_kernel(SolveArgs a) {
       if (threadIdx.x == 0) co_store(scal_w + 0, rr_part);
       if (!(alive = cg_sync(a, ep_cg, &s_flag))) break;
 
-      // the single-reduction CG starts from the whole of r = g: its loads are
-      // issued before the slot sum
+      // the CG on resident rows and the single-reduction form start from the whole of
+      // r = g: its loads are issued before the slot sum
       TV rpre[NPT];
-      if (GRAM && cg1) {
+      if (TAGGED || (GRAM && cg1)) {
 #pragma unroll
         for (int i = 0; i < NPT; ++i) {
           const int c = threadIdx.x + i * kBlock;
@@ -732,7 +736,178 @@ __global__ __launch_bounds__(kBlock) void solve_kernel(SolveArgs a) {
         decision = (rr0 == 0.0) ? 1 : 2;  // stationary point, or NaN
       } else {
         const double stop = a.eps_sub * a.eps_sub * rr0;
-        if (!GRAM && a.aab) {
+        if constexpr (TAGGED) {
+          // ---- CG on resident rows of H, d <= 2048.  A step is a chain of latencies, so it has as few
+          // links as the recurrences allow: every thread keeps its columns of the full
+          // vectors in registers (LDS holds the one that is multiplied), the first wave's
+          // lanes i < nown finish the owned rows and their sums without a barrier, the
+          // exchanged vector (d <= 2048) and scalars travel as tagged values, and every
+          // wave adds the scalars itself.  Each workgroup adds in the same order, so all
+          // take the same steps.  4096 x 256: 4.0 us a step with the barrier forms below.
+          const int tid = threadIdx.x, lane = lane_id();
+          const bool own = tid < nown;
+          const double lt = a.lam;
+          bool ok = true;  // this thread met no timeout
+          // owned row tid of H v (0 elsewhere)
+          auto product = [&](const double* v) {
+            res.dots(v, a.dpad, s_res);
+            lds_barrier();
+            return own ? res.total(s_res, tid) : 0.0;
+          };
+          // this thread's columns of the vector to multiply go to LDS; false after a timeout
+          auto stage = [&](auto&& value) {
+#pragma unroll
+            for (int i = 0; i < NPT; ++i) {
+              const int c = tid + i * kBlock;
+              const double v = value(i);
+              if (c < a.dpad) vbuf[c] = v;
+            }
+            if (!ok) s_flag = 0;
+            lds_barrier();
+            return s_flag != 0;
+          };
+          auto put_scalars = [&](double s0, double s1) {
+            if (tid < 2)
+              tagged_put(a.tags + 2 * (((int64_t)(tag & 1) * Gc + w) * 2 + tid), tid ? s1 : s0, tag);
+          };
+          // sums of the workgroups' scalars under the current tag, for this wave (lane l
+          // takes workgroups l, l + 64, ..; d <= 2048 in 16 columns each: at most 128)
+          constexpr int SL = EPT <= 16 ? 1 : 2;
+          auto get_scalars = [&](double& t0, double& t1) {
+            const tagged_t* ps[2 * SL];
+            bool on[2 * SL];
+            double v[2 * SL];
+#pragma unroll
+            for (int i = 0; i < SL; ++i) {
+              const int q = lane + i * kWave;
+              on[2 * i] = on[2 * i + 1] = q < Gc;
+              ps[2 * i] = a.tags + 2 * (((int64_t)(tag & 1) * Gc + (q < Gc ? q : 0)) * 2);
+              ps[2 * i + 1] = ps[2 * i] + 2;
+            }
+            if (!tagged_get<2 * SL>(ps, on, tag, v, a.err, a.spin_fast)) {
+              ok = false;
+#pragma unroll
+              for (int i = 0; i < 2 * SL; ++i) v[i] = 0.0;
+            }
+            double a0 = v[0], a1 = v[1];
+#pragma unroll
+            for (int i = 1; i < SL; ++i) {
+              a0 += v[2 * i];
+              a1 += v[2 * i + 1];
+            }
+            t0 = wave_sum(a0);
+            t1 = wave_sum(a1);
+          };
+          // All-gather: the owned entry v and two scalars (first wave) to everybody's x and
+          // sums.
+          auto exchange = [&](double v, double s0, double s1, double (&x)[NPT], double& t0,
+                              double& t1) {
+            ++tag;
+            tagged_t* tv = a.tagw + 2 * (int64_t)(tag & 1) * a.dpad;
+            if (own) tagged_put(tv + 2 * (c_lo + tid), v, tag);
+            put_scalars(s0, s1);
+            // the vector first, then the scalars (polled together: 4096 x 256 5.26 instead of
+            // 4.71 ms, every retry repeats all loads)
+            const tagged_t* ps[NPT];
+            bool on[NPT];
+#pragma unroll
+            for (int i = 0; i < NPT; ++i) {
+              const int c = tid + i * kBlock;
+              on[i] = c < d;
+              ps[i] = tv + 2 * (on[i] ? c : 0);
+            }
+            if (!tagged_get<NPT>(ps, on, tag, x, a.err, a.spin_fast)) {
+              ok = false;
+#pragma unroll
+              for (int i = 0; i < NPT; ++i) x[i] = 0.0;
+            }
+            get_scalars(t0, t1);
+          };
+          double z = 0.0, x[NPT];
+          if (cg1) {
+            // single-reduction CG (Chronopoulos-Gear): s = M p by its own recurrence, one
+            // product (w = M r) and one exchange (w, r^T r, w^T r) per step
+            double rv[NPT], sv[NPT], mu = rr0, alpha = 0.0, p = 0.0, t0, nu;
+            if (!(alive = stage([&](int i) { return rv[i] = rpre[i]; }))) break;
+            double rc = own ? vbuf[c_lo + tid] : 0.0;
+            double wc = product(vbuf) + lt * rc;
+            exchange(wc, 0.0, row16_sum(wc * rc), x, t0, nu);
+            alpha = mu / nu;
+            if (!(nu > 0.0) || !isfinite(alpha)) decision = 2;
+            p = rc;
+#pragma unroll
+            for (int i = 0; i < NPT; ++i) sv[i] = x[i];
+            while (decision == 0) {
+              z += alpha * p;
+              if (!(alive = stage([&](int i) { return rv[i] -= alpha * sv[i]; }))) break;
+              ++k;
+              rc = own ? vbuf[c_lo + tid] : 0.0;
+              wc = product(vbuf) + lt * rc;
+              double mu_n, nu_n;
+              exchange(wc, row16_sum(rc * rc), row16_sum(wc * rc), x, mu_n, nu_n);
+              if (mu_n <= stop || k >= a.max_inner) break;
+              const double bt = mu_n / mu;
+              const double den = nu_n - bt * mu_n / alpha;
+              const double an = mu_n / den;
+              if (!(den > 0.0) || !isfinite(an)) {
+                decision = 2;
+                break;
+              }
+              mu = mu_n;
+              alpha = an;
+#pragma unroll
+              for (int i = 0; i < NPT; ++i) sv[i] = x[i] + bt * sv[i];
+              p = rc + bt * p;
+            }
+          } else {
+            // CG with two reductions: p . q among the first waves only (the owners need the
+            // step length), then the new r and r^T r to everybody
+            double pv[NPT], rr = rr0, bc = 0.0, rn = own ? own_r[tid] : 0.0, t1;
+            bool first = true;
+#pragma unroll
+            for (int i = 0; i < NPT; ++i) x[i] = rpre[i];
+            while (true) {
+              if (!(alive = stage([&](int i) {
+                      return pv[i] = first ? x[i] : x[i] + bc * pv[i];
+                    })))
+                break;
+              first = false;
+              const double pc = own ? vbuf[c_lo + tid] : 0.0;
+              const double h = product(vbuf);
+              double rpart = 0.0;
+              ++tag;
+              if (wave_id() == 0) {
+                double pqs;
+                put_scalars(row16_sum(pc * (h + lt * pc)), 0.0);
+                get_scalars(pqs, t1);
+                const double acg = rr / pqs;
+                if (!(pqs > 0.0) || !isfinite(acg)) {
+                  rpart = -1.0;  // breakdown: a negative r^T r tells everybody
+                } else {
+                  z += acg * pc;
+                  rn -= acg * (h + lt * pc);
+                  rpart = row16_sum(rn * rn);
+                }
+              }
+              double rr_new;
+              exchange(rn, rpart, 0.0, x, rr_new, t1);
+              if (rr_new < 0.0) {
+                decision = 2;
+                break;
+              }
+              ++k;
+              if (rr_new <= stop || k >= a.max_inner) break;
+              bc = rr_new / rr;
+              rr = rr_new;
+            }
+          }
+          if (!alive) break;
+          if (own) own_z[tid] = z;
+          // a timeout in the last exchange
+          if (!ok) s_flag = 0;
+          lds_barrier();
+          if (!(alive = s_flag != 0)) break;
+        } else if (!GRAM && a.aab) {
           // AAb_Solver (Algorithm 6) on ((SA)^T SA + lambda I) z = g: Golub-Kahan
           // bidiagonalisation of M = SA started from v = g / ||g||, the
           // sqrt(lambda) I block folded in by Givens rotations.  One pass over

@@ -145,7 +145,12 @@ constexpr size_t kBarLines = 21;
 // tagged, 3.9 by barrier; of 4096: 5.1 against 4.3).
 constexpr int64_t kTagCols = 2048;
 
-// gram_bytes: size of the Gram matrix region (0 when the CG streams SA).
+// Tagged partial vectors of the streaming solvers; they take the Gram matrix's place.
+size_t part_tag_bytes(int Gc, int64_t dpad) {
+  return dpad <= 1024 ? (size_t)Gc * dpad * 16 : 0;
+}
+
+// gram_bytes: size of the Gram matrix region (the tagged partials when the CG streams SA).
 SolveLayout layout(int G, int Gc, int64_t dpad, size_t gram_bytes, int64_t m) {
   SolveLayout L;
   size_t off = 0;
@@ -223,7 +228,8 @@ size_t solve_workspace_bytes(const mihs_handle* h, int64_t n, int64_t d, int64_t
                              int no_gram) {
   (void)n;
   const int G = max_grid(h);
-  return layout(G, G, dpad_for(d), no_gram ? 0 : gram_bytes_for(m, d, mixed), m).total;
+  const size_t gram = no_gram ? 0 : gram_bytes_for(m, d, mixed);
+  return layout(G, G, dpad_for(d), std::max(gram, part_tag_bytes(G, dpad_for(d))), m).total;
 }
 
 int grad_partials(const mihs_handle* h, int64_t n, int64_t d) {
@@ -277,7 +283,9 @@ int launch_solve(const mihs_handle* h, const SolveDesc& s, void* ws, size_t ws_b
   const int64_t g16 = (s.n + 15) / 16, g64 = (s.n + 63) / 64;
   const int64_t g_rows = std::min(g16, std::max<int64_t>(g64, h->num_cu));
   const int NR = solve_resident_rows(s.mixed, ept);
+  bool res_rows = false;
   for (int res = 1; res >= 0 && G == 0; --res) {
+    res_rows = res != 0;
     kern = pick_kernel(s.a_f32, s.mixed, ept, gram, res != 0);
     if (!kern) continue;
     for (int occ_try = kMaxBlocksPerCU; occ_try >= 1; --occ_try) {
@@ -304,7 +312,12 @@ int launch_solve(const mihs_handle* h, const SolveDesc& s, void* ws, size_t ws_b
     }
   }
   if (G == 0) return MIHS_ERR_UNSUPPORTED;
-  const SolveLayout L = layout(G, Gc, dpad, gram ? gram_bytes_for(s.m, s.d, s.mixed) : 0, s.m);
+  // tagged exchange of the streaming solvers: rows in registers, at most 16 owned columns and
+  // 64 workgroups (what one round of the owners' thread grid reads)
+  const bool tag_sa = !gram && res_rows && ept <= 16 && cpw <= 16 && Gc <= 64;
+  const size_t region = gram ? gram_bytes_for(s.m, s.d, s.mixed)
+                             : (tag_sa ? part_tag_bytes(Gc, dpad) : 0);
+  const SolveLayout L = layout(G, Gc, dpad, region, s.m);
   if (ws_bytes < L.total || ws == nullptr) return MIHS_ERR_WORKSPACE;
 
   char* base = (char*)ws;
@@ -352,6 +365,7 @@ int launch_solve(const mihs_handle* h, const SolveDesc& s, void* ws, size_t ws_b
   a.cpw = cpw;
   a.tags = (tagged_t*)(base + L.tags);
   a.tagw = dpad <= kTagCols ? (tagged_t*)(base + L.tagw) : nullptr;
+  a.partT = tag_sa ? (tagged_t*)(base + L.gram) : nullptr;
   a.spin_fast.limit = 1L << 26;  // ~64-clock polls: a few seconds at most
   a.spin_fast.sleep = 1;
   a.spin_idle.limit = 1L << 24;  // ~1000-clock polls while the inner solve runs
@@ -373,8 +387,8 @@ int launch_solve(const mihs_handle* h, const SolveDesc& s, void* ws, size_t ws_b
     if (rc) return rc;
   }
 
-  // barrier words and tags (contiguous up to the Gram matrix; the tags only where used)
-  const int zwords = (int)(((gram ? L.gram : L.tags) - L.bar) / 4);
+  // barrier words and, where used, tags (contiguous)
+  const int zwords = (int)(((gram ? L.gram : tag_sa ? L.gram + region : L.tags) - L.bar) / 4);
   hipLaunchKernelGGL(zero_words, dim3((unsigned)((zwords + 1023) / 1024)), dim3(256), 0, stream,
                      bar, zwords);
   if (hipGetLastError() != hipSuccess) return MIHS_ERR_HIP;

@@ -86,6 +86,7 @@ struct SolveArgs {
   int32_t xw[kXcds];  // gradient-pass row weight of each XCD (row_split_bound)
   tagged_t* tagw;     // 2 x dpad tagged vector entries (null: the vector goes by barrier)
   tagged_t* tags;     // 2 x Gc x 2 tagged scalars
+  tagged_t* partT;    // Gc x dpad tagged partials of SA^T u (null: by barrier, partS)
   BarrierSpin spin_fast, spin_idle;
 };
 
@@ -518,8 +519,9 @@ struct ResidentRows {
     for (int p = 1; p < kResParts; ++p) s += part[p * NR + r];
     return s;
   }
-  // out[0..d) = sum_r u[r] h[r] on this wave's quarter (u in LDS)
-  __device__ __forceinline__ void combine(const double* u, double* out, int d) const {
+  // put(col, sum_r u[r] h[r][col]) for this wave's quarter of [0, d) (u in LDS)
+  template <typename F>
+  __device__ __forceinline__ void combine(const double* u, int d, F&& put) const {
     const int lane = lane_id(), q0 = wave_id() * kWave * EQ;
     double acc[EQ];
 #pragma unroll
@@ -535,7 +537,7 @@ struct ResidentRows {
 #pragma unroll
       for (int vv = 0; vv < L::V; ++vv) {
         const int col = q0 + L::col(j, lane, vv);
-        if (col < d) co_store(out + col, acc[j * L::V + vv]);
+        if (col < d) put(col, acc[j * L::V + vv]);
       }
   }
 };
@@ -570,8 +572,10 @@ __global__ __launch_bounds__(kBlock) void solve_kernel(SolveArgs a) {
   __shared__ double s_part[2 * kQuarterRows * kWavesPerBlock];  // rowpass_quarters exchange
   constexpr int EQ = EPT >= 4 ? EPT / 4 : 1;
   constexpr int NR = resident_rows<TS, EQ>();
-  // tagged exchanges (d <= 2048, owned rows in registers)
-  constexpr bool TAGGED = GRAM && RES && EPT < 64;
+  // tagged exchanges: the Gram forms up to 2048 columns, the streaming ones up to 1024
+  // (2048 spilled 100 registers: Primal-Dual 16384 x 4096 59.7 against 54.7 ms by barrier)
+  // (FP64 rows of 2048 entries fill the registers: by barrier)
+  constexpr bool TAGGED = GRAM && RES && EPT * (int)sizeof(TS) < 256, TAGGED_SA = !GRAM && RES && EPT <= 16;
   __shared__ double s_res[kResParts * NR];  // resident rows' partial products
   __shared__ double s_u[NR], s_y[NR];       // SA rows: u of this step, y of the last one
   __shared__ int s_flag;
@@ -690,7 +694,15 @@ __global__ __launch_bounds__(kBlock) void solve_kernel(SolveArgs a) {
           double ss = 0.0;
 #pragma unroll
           for (int r = 0; r < NR; ++r) ss += s_u[r] * s_u[r];
-          res.combine(s_u, (double*)partS + (int64_t)w * a.dpad, d);
+          if (TAGGED_SA && a.partT) {
+            ++tag;
+            res.combine(s_u, d, [&](int col, double v) {
+              tagged_put(a.partT + 2 * ((int64_t)w * a.dpad + col), v, tag);
+            });
+          } else {
+            double* out = (double*)partS + (int64_t)w * a.dpad;
+            res.combine(s_u, d, [&](int col, double v) { co_store(out + col, v); });
+          }
           return ss;
         } else {
           TV ssq = TV(0);
@@ -721,7 +733,7 @@ __global__ __launch_bounds__(kBlock) void solve_kernel(SolveArgs a) {
       // the CG on resident rows and the single-reduction form start from the whole of
       // r = g: its loads are issued before the slot sum
       TV rpre[NPT];
-      if (TAGGED || (GRAM && cg1)) {
+      if (TAGGED || TAGGED_SA || (GRAM && cg1)) {
 #pragma unroll
         for (int i = 0; i < NPT; ++i) {
           const int c = threadIdx.x + i * kBlock;
@@ -736,6 +748,86 @@ __global__ __launch_bounds__(kBlock) void solve_kernel(SolveArgs a) {
         decision = (rr0 == 0.0) ? 1 : 2;  // stationary point, or NaN
       } else {
         const double stop = a.eps_sub * a.eps_sub * rr0;
+        bool solved = false;
+        const int tid = threadIdx.x, lane = lane_id();
+        const bool own = tid < nown;
+        const double lt = a.lam;
+        bool ok = true;  // this thread met no timeout
+        // owned row tid of H v (0 elsewhere)
+        auto product = [&](const double* v) {
+          res.dots(v, a.dpad, s_res);
+          lds_barrier();
+          return own ? res.total(s_res, tid) : 0.0;
+        };
+        // this thread's columns of the vector to multiply go to LDS; false after a timeout
+        auto stage = [&](auto&& value) {
+#pragma unroll
+          for (int i = 0; i < NPT; ++i) {
+            const int c = tid + i * kBlock;
+            const double v = value(i);
+            if (c < a.dpad) vbuf[c] = v;
+          }
+          if (!ok) s_flag = 0;
+          lds_barrier();
+          return s_flag != 0;
+        };
+        auto put_scalars = [&](double s0, double s1) {
+          if (tid < 2)
+            tagged_put(a.tags + 2 * (((int64_t)(tag & 1) * Gc + w) * 2 + tid), tid ? s1 : s0, tag);
+        };
+        // sums of the workgroups' scalars under the current tag, for this wave (lane l
+        // takes workgroups l, l + 64, ..; d <= 2048 in 16 columns each: at most 128)
+        constexpr int SL = EPT <= 16 ? 1 : 2;
+        auto get_scalars = [&](double& t0, double& t1) {
+          const tagged_t* ps[2 * SL];
+          bool on[2 * SL];
+          double v[2 * SL];
+#pragma unroll
+          for (int i = 0; i < SL; ++i) {
+            const int q = lane + i * kWave;
+            on[2 * i] = on[2 * i + 1] = q < Gc;
+            ps[2 * i] = a.tags + 2 * (((int64_t)(tag & 1) * Gc + (q < Gc ? q : 0)) * 2);
+            ps[2 * i + 1] = ps[2 * i] + 2;
+          }
+          if (!tagged_get<2 * SL>(ps, on, tag, v, a.err, a.spin_fast)) {
+            ok = false;
+#pragma unroll
+            for (int i = 0; i < 2 * SL; ++i) v[i] = 0.0;
+          }
+          double a0 = v[0], a1 = v[1];
+#pragma unroll
+          for (int i = 1; i < SL; ++i) {
+            a0 += v[2 * i];
+            a1 += v[2 * i + 1];
+          }
+          t0 = wave_sum(a0);
+          t1 = wave_sum(a1);
+        };
+        // All-gather: the owned entry v and two scalars (first wave) to everybody's x and
+        // sums.
+        auto exchange = [&](double v, double s0, double s1, double (&x)[NPT], double& t0,
+                            double& t1) {
+          ++tag;
+          tagged_t* tv = a.tagw + 2 * (int64_t)(tag & 1) * a.dpad;
+          if (own) tagged_put(tv + 2 * (c_lo + tid), v, tag);
+          put_scalars(s0, s1);
+          // the vector first, then the scalars (polled together: 4096 x 256 5.26 instead of
+          // 4.71 ms, every retry repeats all loads)
+          const tagged_t* ps[NPT];
+          bool on[NPT];
+#pragma unroll
+          for (int i = 0; i < NPT; ++i) {
+            const int c = tid + i * kBlock;
+            on[i] = c < d;
+            ps[i] = tv + 2 * (on[i] ? c : 0);
+          }
+          if (!tagged_get<NPT>(ps, on, tag, x, a.err, a.spin_fast)) {
+            ok = false;
+#pragma unroll
+            for (int i = 0; i < NPT; ++i) x[i] = 0.0;
+          }
+          get_scalars(t0, t1);
+        };
         if constexpr (TAGGED) {
           // ---- CG on resident rows of H, d <= 2048.  A step is a chain of latencies, so it has as few
           // links as the recurrences allow: every thread keeps its columns of the full
@@ -744,85 +836,6 @@ __global__ __launch_bounds__(kBlock) void solve_kernel(SolveArgs a) {
           // exchanged vector (d <= 2048) and scalars travel as tagged values, and every
           // wave adds the scalars itself.  Each workgroup adds in the same order, so all
           // take the same steps.  4096 x 256: 4.0 us a step with the barrier forms below.
-          const int tid = threadIdx.x, lane = lane_id();
-          const bool own = tid < nown;
-          const double lt = a.lam;
-          bool ok = true;  // this thread met no timeout
-          // owned row tid of H v (0 elsewhere)
-          auto product = [&](const double* v) {
-            res.dots(v, a.dpad, s_res);
-            lds_barrier();
-            return own ? res.total(s_res, tid) : 0.0;
-          };
-          // this thread's columns of the vector to multiply go to LDS; false after a timeout
-          auto stage = [&](auto&& value) {
-#pragma unroll
-            for (int i = 0; i < NPT; ++i) {
-              const int c = tid + i * kBlock;
-              const double v = value(i);
-              if (c < a.dpad) vbuf[c] = v;
-            }
-            if (!ok) s_flag = 0;
-            lds_barrier();
-            return s_flag != 0;
-          };
-          auto put_scalars = [&](double s0, double s1) {
-            if (tid < 2)
-              tagged_put(a.tags + 2 * (((int64_t)(tag & 1) * Gc + w) * 2 + tid), tid ? s1 : s0, tag);
-          };
-          // sums of the workgroups' scalars under the current tag, for this wave (lane l
-          // takes workgroups l, l + 64, ..; d <= 2048 in 16 columns each: at most 128)
-          constexpr int SL = EPT <= 16 ? 1 : 2;
-          auto get_scalars = [&](double& t0, double& t1) {
-            const tagged_t* ps[2 * SL];
-            bool on[2 * SL];
-            double v[2 * SL];
-#pragma unroll
-            for (int i = 0; i < SL; ++i) {
-              const int q = lane + i * kWave;
-              on[2 * i] = on[2 * i + 1] = q < Gc;
-              ps[2 * i] = a.tags + 2 * (((int64_t)(tag & 1) * Gc + (q < Gc ? q : 0)) * 2);
-              ps[2 * i + 1] = ps[2 * i] + 2;
-            }
-            if (!tagged_get<2 * SL>(ps, on, tag, v, a.err, a.spin_fast)) {
-              ok = false;
-#pragma unroll
-              for (int i = 0; i < 2 * SL; ++i) v[i] = 0.0;
-            }
-            double a0 = v[0], a1 = v[1];
-#pragma unroll
-            for (int i = 1; i < SL; ++i) {
-              a0 += v[2 * i];
-              a1 += v[2 * i + 1];
-            }
-            t0 = wave_sum(a0);
-            t1 = wave_sum(a1);
-          };
-          // All-gather: the owned entry v and two scalars (first wave) to everybody's x and
-          // sums.
-          auto exchange = [&](double v, double s0, double s1, double (&x)[NPT], double& t0,
-                              double& t1) {
-            ++tag;
-            tagged_t* tv = a.tagw + 2 * (int64_t)(tag & 1) * a.dpad;
-            if (own) tagged_put(tv + 2 * (c_lo + tid), v, tag);
-            put_scalars(s0, s1);
-            // the vector first, then the scalars (polled together: 4096 x 256 5.26 instead of
-            // 4.71 ms, every retry repeats all loads)
-            const tagged_t* ps[NPT];
-            bool on[NPT];
-#pragma unroll
-            for (int i = 0; i < NPT; ++i) {
-              const int c = tid + i * kBlock;
-              on[i] = c < d;
-              ps[i] = tv + 2 * (on[i] ? c : 0);
-            }
-            if (!tagged_get<NPT>(ps, on, tag, x, a.err, a.spin_fast)) {
-              ok = false;
-#pragma unroll
-              for (int i = 0; i < NPT; ++i) x[i] = 0.0;
-            }
-            get_scalars(t0, t1);
-          };
           double z = 0.0, x[NPT];
           if (cg1) {
             // single-reduction CG (Chronopoulos-Gear): s = M p by its own recurrence, one
@@ -907,6 +920,135 @@ __global__ __launch_bounds__(kBlock) void solve_kernel(SolveArgs a) {
           if (!ok) s_flag = 0;
           lds_barrier();
           if (!(alive = s_flag != 0)) break;
+          solved = true;
+        }
+        if constexpr (TAGGED_SA) {
+          if (a.partT) {
+            // ---- the streaming solvers on resident rows of SA, exchanged the same way: the
+            // workgroups' partial vectors SA^T u go tagged to their columns' owners (a
+            // 16 x 16 thread grid, column x workgroup), the owners' new entries and scalars
+            // tagged to everybody.  2048 x 2048: 24 us an AAb step with rows from memory
+            // and barriers.
+            double z = 0.0, x[NPT], t0, t1;
+            // owned entry tid of sum_w partT (0 elsewhere)
+            auto owned_sum = [&]() {
+              constexpr int NB = 4;  // workgroups per thread (Gc <= 16 NB)
+              const int col = tid % 16, q = tid / 16;
+              const tagged_t* ps[NB];
+              bool on[NB];
+              double v[NB], sum = 0.0;
+#pragma unroll
+              for (int i = 0; i < NB; ++i) {
+                on[i] = col < nown && q + 16 * i < Gc;
+                ps[i] = a.partT +
+                        2 * ((int64_t)(on[i] ? q + 16 * i : 0) * a.dpad + (on[i] ? c_lo + col : 0));
+              }
+              const bool got = tagged_get<NB>(ps, on, tag, v, a.err, a.spin_fast);
+              if (!got) ok = false;
+#pragma unroll
+              for (int i = 0; i < NB; ++i) sum += got && on[i] ? v[i] : 0.0;
+              scratch[tid] = sum;
+              lds_barrier();
+              double s = 0.0;
+              if (own)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) s += scratch[i * 16 + tid];
+              return s;
+            };
+            if (a.aab) {
+              // AAb_Solver (Algorithm 6), see the barrier form below
+              const double theta1 = sqrt(rr0);
+              double theta = 0.0, rho_prev = 1.0, rhobar = 0.0, cs = 0.0, sn = 0.0, phi = 0.0;
+              double dv = 0.0, scale = theta1;
+              bool first = true;
+#pragma unroll
+              for (int i = 0; i < NPT; ++i) x[i] = rpre[i];
+              while (true) {
+                if (!(alive = stage([&](int i) { return x[i] / scale; }))) break;
+                const double vc = own ? vbuf[c_lo + tid] : 0.0;
+                const double ssq = sa_pass(vbuf, -theta / rho_prev, !first);
+                put_scalars(ssq, 0.0);
+                const double my = -owned_sum();  // (M^T y) of the owned column
+                double rho2, th2;
+                get_scalars(rho2, t1);
+                const double rho = sqrt(rho2);
+                double t;
+                if (first) {
+                  rhobar = sqrt(rho * rho + a.lam);
+                  cs = rho / rhobar;
+                  sn = sqrt(a.lam) / rhobar;
+                  phi = theta1 / rhobar;
+                  dv = vc / rhobar;
+                  z = phi * dv;
+                  t = INFINITY;
+                  first = false;
+                } else {
+                  const double lbar = sqrt(a.lam + (sn * theta) * (sn * theta));
+                  const double thetabar = cs * theta;
+                  rhobar = sqrt(rho * rho + lbar * lbar);
+                  cs = rho / rhobar;
+                  sn = lbar / rhobar;
+                  phi = -phi * thetabar / rhobar;
+                  dv = (vc - thetabar * dv) / rhobar;
+                  z = z + phi * dv;
+                  t = fabs(phi * rhobar) / theta1;
+                  ++k;
+                }
+                if (!isfinite(phi) || !isfinite(rhobar)) {
+                  decision = 2;
+                  break;
+                }
+                if (!(t >= a.eps_sub) || k >= a.max_inner || !(rho > 0.0)) break;
+                // w = M^T p - rho v = (M^T y) / rho - rho v on the owned columns
+                const double wc = own ? my / rho - rho * vc : 0.0;
+                exchange(wc, row16_sum(wc * wc), 0.0, x, th2, t1);
+                theta = sqrt(th2);
+                if (!(theta > 0.0)) break;  // w = 0: the iterate is exact
+                rho_prev = rho;
+                scale = theta;
+              }
+            } else {
+              double pv[NPT], rr = rr0, bc = 0.0, rn = own ? own_r[tid] : 0.0;
+              bool first = true;
+#pragma unroll
+              for (int i = 0; i < NPT; ++i) x[i] = rpre[i];
+              while (true) {
+                if (!(alive = stage([&](int i) {
+                        return pv[i] = first ? x[i] : x[i] + bc * pv[i];
+                      })))
+                  break;
+                first = false;
+                const double pc = own ? vbuf[c_lo + tid] : 0.0;
+                const double ssq = sa_pass(vbuf, 0.0, false);
+                put_scalars(ssq, row16_sum(pc * pc));
+                const double mp = -owned_sum();
+                double uu, pp, rr_new;
+                get_scalars(uu, pp);
+                const double pq = uu + a.lam * pp;
+                const double acg = rr / pq;
+                if (!(pq > 0.0) || !isfinite(acg)) {
+                  decision = 2;
+                  break;
+                }
+                z += acg * pc;
+                rn -= acg * (mp + lt * pc);
+                exchange(rn, row16_sum(rn * rn), 0.0, x, rr_new, t0);
+                ++k;
+                if (rr_new <= stop || k >= a.max_inner) break;
+                bc = rr_new / rr;
+                rr = rr_new;
+              }
+            }
+            if (!alive) break;
+            if (own) own_z[tid] = z;
+            // a timeout in the last exchange
+            if (!ok) s_flag = 0;
+            lds_barrier();
+            if (!(alive = s_flag != 0)) break;
+            solved = true;
+          }
+        }
+        if (solved) {
         } else if (!GRAM && a.aab) {
           // AAb_Solver (Algorithm 6) on ((SA)^T SA + lambda I) z = g: Golub-Kahan
           // bidiagonalisation of M = SA started from v = g / ||g||, the

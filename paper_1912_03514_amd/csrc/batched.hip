@@ -18,7 +18,8 @@
 //         d-slice; G = A^T (B - A X) (+ RHS) - X diag(lambda), reduced over the team.
 //   CG    16 CGs in lockstep on (H + lambda_j I) on the first tcg members of the
 //         team (own barrier), each owning a 16-aligned range of columns of q;
-//         per-column step lengths and convergence masks; two barriers each.
+//         per-column step lengths and convergence masks; the members exchange the
+//         per-column sums as tagged words and the vectors across a barrier.
 //   U     per-column heavy-ball step and relative-step stop test.
 //
 // Everything is FP64; all reductions run in a fixed order.

@@ -19,6 +19,8 @@
 //           owners form q = -sum + lambda p and update z, r. -> barrier (Gc)
 //       The stop test ||r|| <= eps_sub ||g|| uses sums every CG workgroup
 //       computes identically, so they all leave the loop together.
+//       Where the group's registers hold the operator's rows (RES) and the vector is
+//       short, the exchanges of C1 and C2 are tagged words instead of barriers.
 //   U   (Gc)     owners apply x+ = x + alpha z + beta (x - x_prev) and write
 //       the relative-step partials.                          -> barrier (all)
 //       Every workgroup then evaluates the same stop test.

@@ -63,6 +63,24 @@ MIHS_HOST_DEVICE inline int64_t row_split_bound(int64_t n, int G, const int32_t*
   return n * pre / tot;
 }
 
+// Slots of the inner solvers' tagged words (device_util.hpp).  Every exchange has a tag of its
+// own, one more than the last, and a word is rewritten by a later exchange that maps to the
+// same slot.  A wave polls for one tag exactly, so no slot may be rewritten while a wave of any
+// workgroup can still wait for what it held.
+//  * Scalars: read by every wave, put by the first one as soon as that has read the last ones.
+//    The streaming solvers put the scalars of two exchanges (tags t, t + 1) between two
+//    workgroup barriers, so another workgroup can be at t + 2 while a slow wave here still
+//    waits for t: four slots, as t + 4 is put only after every t + 3, and those after a
+//    workgroup barrier that follows the reads of t.  (Two slots suffice for the CG on the Gram
+//    matrix, which has a barrier between its reads by all waves and the next put.)
+//  * Vector entries: a workgroup barrier lies between the reads of one vector and the put of
+//    anything that lets another workgroup go beyond the next one: two slots.
+//  * Partial vectors of the streaming solvers: one slot, the barrier of the column sums lies
+//    between the reads and what lets any workgroup go on.
+constexpr unsigned kScalarSlots = 4, kVectorSlots = 2;
+MIHS_HOST_DEVICE constexpr unsigned scalar_slot(unsigned tag) { return tag % kScalarSlots; }
+MIHS_HOST_DEVICE constexpr unsigned vector_slot(unsigned tag) { return tag % kVectorSlots; }
+
 // Measures each XCD's streaming time and sets h->row_weight from it
 // (mihs_calibrate_rows).
 int calibrate_rows(mihs_handle* h);

@@ -161,8 +161,8 @@ SolveLayout layout(int G, int Gc, int64_t dpad, size_t gram_bytes, int64_t m) {
   L.xp = off;    off = align_up(off + (size_t)dpad * 8, 256);
   L.bar = off;   off = align_up(off + kBarLines * 128, 256);
   // tagged scalars and vector entries, cleared with the barrier words by every launch
-  L.tags = off;  off += 2 * (size_t)Gc * 2 * 16;
-  L.tagw = off;  off += dpad <= kTagCols ? 2 * (size_t)dpad * 16 : 0;
+  L.tags = off;  off += kScalarSlots * (size_t)Gc * 2 * 16;
+  L.tagw = off;  off += dpad <= kTagCols ? kVectorSlots * (size_t)dpad * 16 : 0;
   off = align_up(off, 256);
   L.gram = off;  off = align_up(off + gram_bytes, 256);
   L.yrow = off;  off = align_up(off + (size_t)m * 8, 256);

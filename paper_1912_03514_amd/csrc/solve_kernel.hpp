@@ -86,8 +86,8 @@ struct SolveArgs {
   int d, dpad, G, Gc, cpw;
   int cg_hier;        // inner-solve group large enough for the two-level barrier
   int32_t xw[kXcds];  // gradient-pass row weight of each XCD (row_split_bound)
-  tagged_t* tagw;     // 2 x dpad tagged vector entries (null: the vector goes by barrier)
-  tagged_t* tags;     // 2 x Gc x 2 tagged scalars
+  tagged_t* tagw;     // kVectorSlots x dpad tagged vector entries (null: by barrier)
+  tagged_t* tags;     // kScalarSlots x Gc x 2 tagged scalars
   tagged_t* partT;    // Gc x dpad tagged partials of SA^T u (null: by barrier, partS)
   BarrierSpin spin_fast, spin_idle;
 };
@@ -775,7 +775,8 @@ __global__ __launch_bounds__(kBlock) void solve_kernel(SolveArgs a) {
         };
         auto put_scalars = [&](double s0, double s1) {
           if (tid < 2)
-            tagged_put(a.tags + 2 * (((int64_t)(tag & 1) * Gc + w) * 2 + tid), tid ? s1 : s0, tag);
+            tagged_put(a.tags + 2 * (((int64_t)scalar_slot(tag) * Gc + w) * 2 + tid),
+                       tid ? s1 : s0, tag);
         };
         // sums of the workgroups' scalars under the current tag, for this wave (lane l
         // takes workgroups l, l + 64, ..; d <= 2048 in 16 columns each: at most 128)
@@ -788,7 +789,7 @@ __global__ __launch_bounds__(kBlock) void solve_kernel(SolveArgs a) {
           for (int i = 0; i < SL; ++i) {
             const int q = lane + i * kWave;
             on[2 * i] = on[2 * i + 1] = q < Gc;
-            ps[2 * i] = a.tags + 2 * (((int64_t)(tag & 1) * Gc + (q < Gc ? q : 0)) * 2);
+            ps[2 * i] = a.tags + 2 * (((int64_t)scalar_slot(tag) * Gc + (q < Gc ? q : 0)) * 2);
             ps[2 * i + 1] = ps[2 * i] + 2;
           }
           if (!tagged_get<2 * SL>(ps, on, tag, v, a.err, a.spin_fast)) {
@@ -810,7 +811,7 @@ __global__ __launch_bounds__(kBlock) void solve_kernel(SolveArgs a) {
         auto exchange = [&](double v, double s0, double s1, double (&x)[NPT], double& t0,
                             double& t1) {
           ++tag;
-          tagged_t* tv = a.tagw + 2 * (int64_t)(tag & 1) * a.dpad;
+          tagged_t* tv = a.tagw + 2 * (int64_t)vector_slot(tag) * a.dpad;
           if (own) tagged_put(tv + 2 * (c_lo + tid), v, tag);
           put_scalars(s0, s1);
           // the vector first, then the scalars (polled together: 4096 x 256 5.26 instead of

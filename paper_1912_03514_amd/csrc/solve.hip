@@ -178,28 +178,6 @@ size_t gram_bytes_for(int64_t m, int64_t d, int mixed) {
 
 int max_grid(const mihs_handle* h) { return h->num_cu * kMaxBlocksPerCU; }
 
-// Size of the inner-solve subgroup.  With the operator's rows in registers (`res`) it is the
-// fewest workgroups that hold them (NR rows each): a step is then bound by its exchange,
-// which costs more the more workgroups take part (one barrier and gather, 2048 entries: 2.9
-// us among 64, 3.6 among 128, 3.9 among 256).  Otherwise every step streams the operator:
-// 256 workgroups for 8 MB and more, fewer below, at least a few rows each.  No workgroup
-// owns more than 16 columns unless the grid is that small: the owners add the gradient's
-// partial vectors, 16 columns of 256 partials in one round of loads.  Returns 0 when the
-// rows do not fit (res).
-int pick_cg_groups(int64_t m, int64_t d, int sa_bytes, int G, bool gram, bool res, int NR) {
-  const int64_t rows = gram ? d : m, by_cols = (d + 15) / 16;
-  int64_t gc;
-  if (res) {
-    gc = std::max((rows + NR - 1) / NR, by_cols);
-    if (gc > G) gc = G;
-    return gc * NR >= rows ? (int)gc : 0;
-  }
-  const double mb = (double)rows * (double)d * sa_bytes / (1024.0 * 1024.0);
-  gc = mb >= 8.0 ? 256 : (mb >= 4.0 ? 64 : (mb >= 1.0 ? 32 : 16));
-  gc = std::max(std::min(gc, (m + 3) / 4), by_cols);
-  return (int)std::max<int64_t>(1, std::min<int64_t>(gc, G));
-}
-
 }  // namespace
 
 // ---- scratch of the entry point without a workspace argument -------------
@@ -271,50 +249,27 @@ int launch_solve(const mihs_handle* h, const SolveDesc& s, void* ws, size_t ws_b
   // AAb_Solver needs M v and M^T p separately: it always streams SA
   const bool gram = !s.no_gram && !s.aab && use_gram(s.m, s.d);
   const int64_t dpad = dpad_for(s.d);
-  // Pick the kernel (operator rows in registers where they fit) and the grid: try two
-  // workgroups per CU, then one; the inner-solve group size (and with it the LDS request)
-  // depends on the grid.
   SolveKernel kern = nullptr;
-  int G = 0, Gc = 0, cpw = 0;
-  size_t shmem = 0;
-  // keep >= 16 rows of A per workgroup (64 left three quarters of the CUs idle in the
-  // Primal-Dual dual steps, which pass over 4096 rows: 82 against 71 ms at 16384 x 4096),
-  // and >= 64 before a CU takes a second one (more partial vectors to add)
-  const int64_t g16 = (s.n + 15) / 16, g64 = (s.n + 63) / 64;
-  const int64_t g_rows = std::min(g16, std::max<int64_t>(g64, h->num_cu));
-  const int NR = solve_resident_rows(s.mixed, ept);
-  bool res_rows = false;
-  for (int res = 1; res >= 0 && G == 0; --res) {
-    res_rows = res != 0;
-    kern = pick_kernel(s.a_f32, s.mixed, ept, gram, res != 0);
-    if (!kern) continue;
-    for (int occ_try = kMaxBlocksPerCU; occ_try >= 1; --occ_try) {
-      int g = h->num_cu * occ_try;
-      if ((int64_t)g > g_rows) g = (int)(g_rows < 1 ? 1 : g_rows);
-      const int gc = pick_cg_groups(s.m, s.d, s.mixed ? 4 : 8, g, gram, res != 0, NR);
-      if (gc == 0) continue;
-      const int cp = (int)((s.d + gc - 1) / gc);
-      const size_t sh = (2 * (size_t)dpad + 6 * (size_t)cp + kBlock) * sizeof(double);
-      if (sh > 152 * 1024) continue;
-      if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)sh) != hipSuccess)
-        return MIHS_ERR_HIP;
-      int occ = 0;
-      if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kern, kBlock, sh) != hipSuccess)
-        return MIHS_ERR_HIP;
-      if (occ >= occ_try || (occ >= 1 && (int64_t)g <= (int64_t)h->num_cu * occ)) {
-        G = g;
-        Gc = gc;
-        cpw = cp;
-        shmem = sh;
-        break;
-      }
-    }
-  }
-  if (G == 0) return MIHS_ERR_UNSUPPORTED;
+  bool hip_error = false;
+  const SolveShape shape = pick_solve_shape(
+      s.n, s.d, s.m, s.mixed ? 4 : 8, ept, gram, h->num_cu, [&](bool res, size_t lds) {
+        kern = pick_kernel(s.a_f32, s.mixed, ept, gram, res);
+        int occ = 0;
+        hip_error = !kern ||
+                    hipFuncSetAttribute((const void*)kern,
+                                        hipFuncAttributeMaxDynamicSharedMemorySize,
+                                        (int)lds) != hipSuccess ||
+                    hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kern, kBlock, lds) !=
+                        hipSuccess;
+        return hip_error ? -1 : occ;
+      });
+  if (hip_error) return MIHS_ERR_HIP;
+  if (shape.G == 0) return MIHS_ERR_UNSUPPORTED;
+  const int G = shape.G, Gc = shape.Gc, cpw = shape.cpw;
+  const size_t shmem = shape.lds;
   // tagged exchange of the streaming solvers: rows in registers, at most 16 owned columns and
   // 64 workgroups (what one round of the owners' thread grid reads)
-  const bool tag_sa = !gram && res_rows && ept <= 16 && cpw <= 16 && Gc <= 64;
+  const bool tag_sa = !gram && shape.res && ept <= 16 && cpw <= 16 && Gc <= 64;
   const size_t region = gram ? gram_bytes_for(s.m, s.d, s.mixed)
                              : (tag_sa ? part_tag_bytes(Gc, dpad) : 0);
   const SolveLayout L = layout(G, Gc, dpad, region, s.m);

@@ -35,12 +35,12 @@
 
 #include "device_util.hpp"
 #include "internal.hpp"
+#include "solve_shape.hpp"
 
 namespace mihs {
 
 constexpr int kScal = 8;           // scalar partial slots per workgroup
 constexpr double kCg1MaxCond = 1e5;  // single-reduction CG up to this trace(H)/lambda
-constexpr int kMaxBlocksPerCU = 2;
 // Rows per group in rowpass_quarters: 128 KB of a 4096-wide matrix in flight per CU in
 // either type (FP32, 2^20 x 4096: 4 rows with the next group prefetched 3.35 ms a pass,
 // 8 without 3.20).
@@ -424,14 +424,6 @@ __device__ __forceinline__ void rowdots(const TH* __restrict__ H, int64_t ldh, i
 // The four waves split every row into quarters of 64 * EQ columns, so each reads only its
 // quarter of the vector from LDS and, for SA, accumulates only its quarter of SA^T u.
 
-// Rows a workgroup can keep: 256 registers per lane, at most 16 rows.
-template <typename TS, int EQ>
-constexpr int resident_rows() {
-  int r = 16;
-  while (r * EQ * (int)sizeof(TS) / 4 > 256) r /= 2;
-  return r;
-}
-
 // Sums of N values (N = 1, 2, 4, 8 or 16) over each row of 16 lanes at once: a stage either
 // halves the number of values per lane (each lane keeps the half that its lane bit names
 // and adds the partner's) or, when one is left, adds the partner's.  Lane l ends with value
@@ -573,7 +565,7 @@ __global__ __launch_bounds__(kBlock) void solve_kernel(SolveArgs a) {
   __shared__ double s_red[2 * kWavesPerBlock];
   __shared__ double s_part[2 * kQuarterRows * kWavesPerBlock];  // rowpass_quarters exchange
   constexpr int EQ = EPT >= 4 ? EPT / 4 : 1;
-  constexpr int NR = resident_rows<TS, EQ>();
+  constexpr int NR = resident_rows(sizeof(TS), EPT);
   // tagged exchanges: the Gram forms up to 2048 columns, the streaming ones up to 1024
   // (2048 spilled 100 registers: Primal-Dual 16384 x 4096 59.7 against 54.7 ms by barrier)
   // (FP64 rows of 2048 entries fill the registers: by barrier)
@@ -1433,20 +1425,12 @@ __global__ __launch_bounds__(kBlock) void solve_kernel(SolveArgs a) {
   }
 }
 
-// Which instances exist: rows of the operator in registers (RES) wherever the launch can make
-// them fit, which for the Gram matrix is always but for FP64 rows of 4096 entries (8 per
-// workgroup); the streaming operators have both forms, as a sketch may have any number of rows.
-template <typename TS, int EPT, bool GRAM, bool RES>
-constexpr bool solve_instance() {
-  return !GRAM || RES == !(sizeof(TS) == 8 && EPT == 64);
-}
-
 typedef void (*SolveKernel)(SolveArgs);
 
 template <typename TA, typename TS, bool GRAM, bool RES, int EPT = 1>
 SolveKernel pick_by_ept(int ept) {
   if (ept == EPT) {
-    if constexpr (solve_instance<TS, EPT, GRAM, RES>())
+    if constexpr (solve_instance(sizeof(TS), EPT, GRAM, RES))
       return solve_kernel<TA, TS, double, EPT, GRAM, RES>;
     else
       return nullptr;
@@ -1455,14 +1439,6 @@ SolveKernel pick_by_ept(int ept) {
     return pick_by_ept<TA, TS, GRAM, RES, 2 * EPT>(ept);
   else
     return nullptr;
-}
-
-// Rows per workgroup that the RES form keeps.
-inline int solve_resident_rows(int mixed, int ept) {
-  const int eq = ept >= 4 ? ept / 4 : 1, bytes = mixed ? 4 : 8;
-  int r = 16;
-  while (r * eq * bytes / 4 > 256) r /= 2;
-  return r;
 }
 
 // The instances are compiled in four files, by the types of A and of the inner operator.

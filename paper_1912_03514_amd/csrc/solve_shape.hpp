@@ -1,0 +1,104 @@
+// Launch shape of the persistent solve (host only, no HIP calls): which form of the kernel runs,
+// on how many workgroups, and with how much LDS.
+#pragma once
+
+#include <stddef.h>
+#include <stdint.h>
+
+#include <algorithm>
+
+namespace mihs {
+
+constexpr int kMaxBlocksPerCU = 2;
+constexpr size_t kSolveLds = 152 * 1024;  // dynamic LDS at most (the kernel has up to 3 KB more)
+
+// Rows of the inner operator that a workgroup keeps in registers (one quarter of each row per
+// wave, `ept / 4` entries per lane): 256 registers per lane, at most 16 rows.
+constexpr int resident_rows(int bytes, int ept) {
+  const int eq = ept >= 4 ? ept / 4 : 1;
+  int r = 16;
+  while (r * eq * bytes / 4 > 256) r /= 2;
+  return r;
+}
+
+// Which forms of the kernel exist.  The streaming operators have both, as a sketch may have any
+// number of rows.  Gram matrices are resident wherever 16 rows fit a workgroup's registers (not
+// FP64 rows of 4096 entries) and the grid has d / 16 workgroups.  A whole GPU always has; the
+// form that reads H in every step is left for the widths that a partition's CUs may not hold
+// (the smallest has 32: d > 512).
+constexpr bool solve_instance(int bytes, int ept, bool gram, bool res) {
+  return !gram || (res ? resident_rows(bytes, ept) == 16 : ept >= 16);
+}
+
+// Size of the inner-solve subgroup.  With the operator's rows in registers (`res`) it is the
+// fewest workgroups that hold them (NR rows each): a step is then bound by its exchange,
+// which costs more the more workgroups take part (one barrier and gather, 2048 entries: 2.9
+// us among 64, 3.6 among 128, 3.9 among 256).  Otherwise every step streams the operator:
+// 256 workgroups for 8 MB and more, fewer below, at least a few rows each.  No workgroup
+// owns more than 16 columns unless the grid is that small: the owners add the gradient's
+// partial vectors, 16 columns of 256 partials in one round of loads.  Returns 0 when the
+// rows do not fit (res).
+inline int pick_cg_groups(int64_t m, int64_t d, int sa_bytes, int G, bool gram, bool res, int NR) {
+  const int64_t rows = gram ? d : m, by_cols = (d + 15) / 16;
+  int64_t gc;
+  if (res) {
+    gc = std::max((rows + NR - 1) / NR, by_cols);
+    if (gc > G) gc = G;
+    return gc * NR >= rows ? (int)gc : 0;
+  }
+  const double mb = (double)rows * (double)d * sa_bytes / (1024.0 * 1024.0);
+  gc = mb >= 8.0 ? 256 : (mb >= 4.0 ? 64 : (mb >= 1.0 ? 32 : 16));
+  gc = std::max(std::min(gc, (m + 3) / 4), by_cols);
+  return (int)std::max<int64_t>(1, std::min<int64_t>(gc, G));
+}
+
+struct SolveShape {
+  bool res = false;   // the inner operator's rows stay in registers
+  int G = 0, Gc = 0;  // workgroups, of which the first Gc run the inner solve (G = 0: none fits)
+  int cpw = 0;        // columns owned per inner-solve workgroup
+  size_t lds = 0;     // dynamic LDS bytes
+};
+
+// occupancy(res, lds): workgroups of that form per CU, or < 0 on an error (then G stays 0).
+// Resident rows where they fit; two workgroups per CU, then one.
+template <typename Occ>
+SolveShape pick_solve_shape(int64_t n, int64_t d, int64_t m, int bytes, int ept, bool gram,
+                            int num_cu, Occ&& occupancy) {
+  SolveShape S;
+  const int64_t dpad = 64 * (int64_t)ept;
+  // keep >= 16 rows of A per workgroup (64 left three quarters of the CUs idle in the
+  // Primal-Dual dual steps, which pass over 4096 rows: 82 against 71 ms at 16384 x 4096),
+  // and >= 64 before a CU takes a second one (more partial vectors to add)
+  const int64_t g16 = (n + 15) / 16, g64 = (n + 63) / 64;
+  const int64_t g_rows = std::max<int64_t>(1, std::min(g16, std::max<int64_t>(g64, num_cu)));
+  const int NR = resident_rows(bytes, ept);
+  for (int res = 1; res >= 0; --res) {
+    if (!solve_instance(bytes, ept, gram, res != 0)) continue;
+    // a Gram matrix is as large as d says, however few rows A has (Primal-Dual solves may have
+    // fewer rows than columns): the resident form takes the workgroups that hold it, some
+    // without rows of A
+    const int64_t need = gram && res ? (d + NR - 1) / NR : 1;
+    for (int occ_try = kMaxBlocksPerCU; occ_try >= 1; --occ_try) {
+      const int64_t most = (int64_t)num_cu * occ_try;
+      const int g = (int)std::min(most, std::max(g_rows, need));
+      const int gc = pick_cg_groups(m, d, bytes, g, gram, res != 0, NR);
+      if (gc == 0) continue;
+      const int cp = (int)((d + gc - 1) / gc);
+      const size_t lds = (2 * (size_t)dpad + 6 * (size_t)cp + 256) * sizeof(double);
+      if (lds > kSolveLds) continue;
+      const int occ = occupancy(res != 0, lds);
+      if (occ < 0) return S;
+      if (occ >= occ_try || (occ >= 1 && (int64_t)g <= (int64_t)num_cu * occ)) {
+        S.res = res != 0;
+        S.G = g;
+        S.Gc = gc;
+        S.cpw = cp;
+        S.lds = lds;
+        return S;
+      }
+    }
+  }
+  return S;
+}
+
+}  // namespace mihs

@@ -333,7 +333,9 @@ __global__ void srht_sign_words_kernel(uint32_t* words, int64_t nwords, uint32_t
   words[w] = v;
 }
 
-template <typename TA, typename TY, int LOGB, int NS, typename TS>
+// WIDE: rows so long that a block spans 2 GiB and more, addressed by 64-bit pointers instead of
+// 32-bit offsets into the block.
+template <typename TA, typename TY, int LOGB, int NS, typename TS, bool WIDE>
 __global__ __launch_bounds__(kFusedThreads) void srht_fused_kernel(
     const TA* __restrict__ A, int64_t lda, int64_t d, const uint32_t* __restrict__ signw,
     const int* __restrict__ idx, int64_t m, int64_t nblk, int nparts, TY* __restrict__ P,
@@ -376,16 +378,24 @@ __global__ __launch_bounds__(kFusedThreads) void srht_fused_kernel(
   const int32_t row32 = (int32_t)(32 * lda * (int64_t)sizeof(TA));  // bytes between rows g + 32 i
   const int32_t blk_bytes = (int32_t)(B * lda * (int64_t)sizeof(TA));
   auto load_block = [&](int64_t b) {
-    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)(A + b * B * lda), (short)0, blk_bytes, kBufferRsrcWord3);
+    if constexpr (WIDE) {
+      const TA* p = A + (b * B + g) * lda + (col_ok ? col : 0);
 #pragma unroll
-    for (int i = 0; i < R; ++i) {
-      if constexpr (sizeof(TA) == 8) {
-        const auto v = __builtin_amdgcn_raw_buffer_load_b64(rs, lane_off, i * row32, kBufferNt);
-        xa[i] = __builtin_bit_cast(TA, v);
-      } else {
-        const auto v = __builtin_amdgcn_raw_buffer_load_b32(rs, lane_off, i * row32, 0);
-        xa[i] = __builtin_bit_cast(TA, v);
+      for (int i = 0; i < R; ++i)
+        xa[i] = sizeof(TA) == 8 ? __builtin_nontemporal_load(p + (int64_t)(32 * i) * lda)
+                                : p[(int64_t)(32 * i) * lda];
+    } else {
+      const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+          (void*)(A + b * B * lda), (short)0, blk_bytes, kBufferRsrcWord3);
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        if constexpr (sizeof(TA) == 8) {
+          const auto v = __builtin_amdgcn_raw_buffer_load_b64(rs, lane_off, i * row32, kBufferNt);
+          xa[i] = __builtin_bit_cast(TA, v);
+        } else {
+          const auto v = __builtin_amdgcn_raw_buffer_load_b32(rs, lane_off, i * row32, 0);
+          xa[i] = __builtin_bit_cast(TA, v);
+        }
       }
     }
   };
@@ -1126,7 +1136,7 @@ struct SrhtFusedPlan {
   bool ok = false;
   int logb = 0, ns = 0, nparts = 1;
   int64_t nblk = 0, strips = 0;
-  size_t idx_bytes = 0, sign_bytes = 0, part_bytes = 0, lds = 0;
+  size_t idx_bytes = 0, sign_bytes = 0, part_bytes = 0;
   size_t total() const { return idx_bytes + sign_bytes + part_bytes; }
 };
 
@@ -1161,8 +1171,6 @@ SrhtFusedPlan srht_fused_plan(const mihs_handle* h, int64_t n, int64_t d, int64_
   F.idx_bytes = align_up((size_t)m * 4, 256);
   F.sign_bytes = align_up((size_t)(n / 32) * 4, 256);
   F.part_bytes = F.nparts > 1 ? align_up((size_t)F.nparts * m * d * ty_bytes, 256) : 0;
-  F.lds = (size_t)fused_row(1 << F.logb, f32 ? 32 : 16) * kFusedW * ty_bytes +
-          (size_t)groups * F.ns * 4;
   return F;
 }
 
@@ -1174,28 +1182,35 @@ int launch_srht_fused(const SrhtFusedPlan& F, const TA* A, int64_t lda, int64_t 
   if (fused_pair<TA>() == 2)
     wgs = ceil_div((F.strips + 1) / 2 * F.nparts, kXcds) * 2 * kXcds;
   const dim3 grid((unsigned)wgs);
-  auto go = [&](auto kern) -> int {
+  auto go = [&](auto kern, int ns) -> int {
+    const size_t lds = ((size_t)fused_row(1 << LOGB, sizeof(TY) == 4 ? 32 : 16) * kFusedW) *
+                           sizeof(TY) + (size_t)fused_groups<TY>() * ns * 4;
     if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)F.lds) != hipSuccess)
+                            (int)lds) != hipSuccess)
       return MIHS_ERR_HIP;
-    hipLaunchKernelGGL(kern, grid, dim3(kFusedThreads), F.lds, st, A, lda, d, signw, idx, m,
+    hipLaunchKernelGGL(kern, grid, dim3(kFusedThreads), lds, st, A, lda, d, signw, idx, m,
                        F.nblk, F.nparts, P, d, SA, ldsa, scale);
     return MIHS_OK;
   };
   int rc = MIHS_ERR_UNSUPPORTED;
-  if constexpr (sizeof(TY) == 4) {
+  // the 32-bit offsets of a block's rows reach 2 GiB; longer blocks (FP64 rows of 2 MiB and
+  // more at 1024 rows) take the addressing by pointers, in one form for all sample counts
+  // (1024 x 262144 FP64, m = 3000: 4.8 ms, 16.9 in two stages)
+  if ((double)(1LL << LOGB) * (double)lda * sizeof(TA) >= 2147483647.0) {
+    rc = go(srht_fused_kernel<TA, TY, LOGB, 32, TS, true>, 32);
+  } else if constexpr (sizeof(TY) == 4) {
     switch (F.ns) {
-      case 4: rc = go(srht_fused_kernel<TA, TY, LOGB, 4, TS>); break;
-      case 8: rc = go(srht_fused_kernel<TA, TY, LOGB, 8, TS>); break;
-      case 16: rc = go(srht_fused_kernel<TA, TY, LOGB, 16, TS>); break;
-      case 24: rc = go(srht_fused_kernel<TA, TY, LOGB, 24, TS>); break;
-      case 32: rc = go(srht_fused_kernel<TA, TY, LOGB, 32, TS>); break;
+      case 4: rc = go(srht_fused_kernel<TA, TY, LOGB, 4, TS, false>, 4); break;
+      case 8: rc = go(srht_fused_kernel<TA, TY, LOGB, 8, TS, false>, 8); break;
+      case 16: rc = go(srht_fused_kernel<TA, TY, LOGB, 16, TS, false>, 16); break;
+      case 24: rc = go(srht_fused_kernel<TA, TY, LOGB, 24, TS, false>, 24); break;
+      case 32: rc = go(srht_fused_kernel<TA, TY, LOGB, 32, TS, false>, 32); break;
     }
   } else {
     switch (F.ns) {
-      case 8: rc = go(srht_fused_kernel<TA, TY, LOGB, 8, TS>); break;
-      case 16: rc = go(srht_fused_kernel<TA, TY, LOGB, 16, TS>); break;
-      case 32: rc = go(srht_fused_kernel<TA, TY, LOGB, 32, TS>); break;
+      case 8: rc = go(srht_fused_kernel<TA, TY, LOGB, 8, TS, false>, 8); break;
+      case 16: rc = go(srht_fused_kernel<TA, TY, LOGB, 16, TS, false>, 16); break;
+      case 32: rc = go(srht_fused_kernel<TA, TY, LOGB, 32, TS, false>, 32); break;
     }
   }
   if (rc) return rc;
@@ -1208,9 +1223,8 @@ int launch_srht_fused(const SrhtFusedPlan& F, const TA* A, int64_t lda, int64_t 
 template <typename TA, typename TY, typename TS>
 int run_srht(const mihs_handle* h, const TA* A, int64_t n, int64_t d, int64_t lda, int64_t m,
              uint32_t seed, TS* SA, int64_t ldsa, char* ws, size_t ws_bytes, hipStream_t st) {
-  SrhtFusedPlan F = srht_fused_plan(h, n, d, m, (int)sizeof(TY));
-  // a block's bytes must fit the 32-bit buffer range of the row loads
-  if (F.ok && (double)(1LL << F.logb) * (double)lda * sizeof(TA) >= 2147483647.0) F.ok = false;
+  // (the workspace query knows no row stride, so the form must not depend on it)
+  const SrhtFusedPlan F = srht_fused_plan(h, n, d, m, (int)sizeof(TY));
   if (F.ok) {
     if (ws_bytes < F.total()) return MIHS_ERR_WORKSPACE;
     int* idx = (int*)ws;

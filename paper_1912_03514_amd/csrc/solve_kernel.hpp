@@ -112,17 +112,16 @@ __device__ __forceinline__ void rowpass(const TM* __restrict__ M, int64_t ld, in
                                         double cs = 1.0, double* uout = nullptr) {
   using L = RowLayout<TM, EPT>;
   const int lane = lane_id();
+  constexpr bool CLAMP = EPT < 64;
+  // (opaque: the clamped columns are not kept between passes)
+  if constexpr (CLAMP) asm volatile("" : "+s"(d));
   for (int64_t row = r0 + (int64_t)wave_id() * R; row < r1; row += (int64_t)kWavesPerBlock * R) {
+    // (rows past the range read its last one; their u is zero)
     TM rv[R][EPT];
 #pragma unroll
-    for (int t = 0; t < R; ++t) {
-      if (row + t < r1) {
-        load_row<TM, EPT, NT>(M + (row + t) * ld, d, lane, rv[t]);
-      } else {
-#pragma unroll
-        for (int e = 0; e < EPT; ++e) rv[t][e] = TM(0);
-      }
-    }
+    for (int t = 0; t < R; ++t)
+      load_row<TM, EPT, NT, CLAMP>(M + (R == 1 ? row : min(row + t, r1 - 1)) * ld, 0, d, lane, rv[t]);
+    if (CLAMP) clear_tail<TM, EPT, R>(0, d, lane, rv);
     TV dot[R];
 #pragma unroll
     for (int t = 0; t < R; ++t) dot[t] = TV(0);
@@ -168,7 +167,8 @@ __device__ __forceinline__ void rowpass_quarters(const TM* __restrict__ M, int64
   constexpr bool PF = R * EQ * (int)sizeof(TM) <= 256;
   const int lane = lane_id(), w = wave_id();
   const int q0 = w * kWave * EQ;  // first column of this wave's quarter
-  const int dq = d - q0;          // valid columns from q0 (may be <= 0)
+  if (r0 >= r1) return;
+  asm volatile("" : "+s"(d));  // (opaque: the clamped columns are not kept between passes)
   double vr[EQ];
 #pragma unroll
   for (int j = 0; j < L::J; ++j)
@@ -176,14 +176,8 @@ __device__ __forceinline__ void rowpass_quarters(const TM* __restrict__ M, int64
     for (int vv = 0; vv < L::V; ++vv) vr[j * L::V + vv] = v[q0 + L::col(j, lane, vv)];
   auto load_group = [&](int64_t row0, TM (&buf)[R][EQ]) {
 #pragma unroll
-    for (int t = 0; t < R; ++t) {
-      if (row0 + t < r1) {
-        load_row<TM, EQ, NT>(M + (row0 + t) * ld + q0, dq, lane, buf[t]);
-      } else {
-#pragma unroll
-        for (int e = 0; e < EQ; ++e) buf[t][e] = TM(0);
-      }
-    }
+    for (int t = 0; t < R; ++t)
+      load_row<TM, EQ, NT>(M + min(row0 + t, r1 - 1) * ld, q0, d, lane, buf[t]);
   };
   TM cur[R][EQ];
   if constexpr (PF) load_group(r0, cur);
@@ -192,6 +186,7 @@ __device__ __forceinline__ void rowpass_quarters(const TM* __restrict__ M, int64
     TM nxt[R][EQ];
     if constexpr (PF) load_group(row + R, nxt);
     else load_group(row, cur);
+    clear_tail<TM, EQ, R>(q0, d, lane, cur);
     double dot[R];
 #pragma unroll
     for (int t = 0; t < R; ++t) {
@@ -364,15 +359,11 @@ __device__ __forceinline__ void rowdots_r(const TH* __restrict__ H, int64_t ldh,
   const int lane = lane_id();
   for (int c = r0 + wave_id() * R; c < r1; c += kWavesPerBlock * R) {
     TH rv[R][EPT];
+    constexpr bool CLAMP = EPT < 64;
 #pragma unroll
-    for (int t = 0; t < R; ++t) {
-      if (c + t < r1) {
-        load_row<TH, EPT, false>(H + (int64_t)(c + t) * ldh, d, lane, rv[t]);
-      } else {
-#pragma unroll
-        for (int e = 0; e < EPT; ++e) rv[t][e] = TH(0);
-      }
-    }
+    for (int t = 0; t < R; ++t)
+      load_row<TH, EPT, false, CLAMP>(H + (int64_t)(R == 1 ? c : min(c + t, r1 - 1)) * ldh, 0, d, lane, rv[t]);
+    if (CLAMP) clear_tail<TH, EPT, R>(0, d, lane, rv);
     TV dot[R];
 #pragma unroll
     for (int t = 0; t < R; ++t) dot[t] = TV(0);
@@ -469,12 +460,13 @@ struct ResidentRows {
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
       if (r0 + r < r1) {
-        load_row<TS, EQ, false>(M + (r0 + r) * ld + q0, d - q0, lane_id(), h[r]);
+        load_row<TS, EQ, false>(M + (r0 + r) * ld, q0, d, lane_id(), h[r]);
       } else {
 #pragma unroll
         for (int e = 0; e < EQ; ++e) h[r][e] = TS(0);
       }
     }
+    clear_tail<TS, EQ, NR>(q0, d, lane_id(), h);
   }
   // Entry e of row r.  FP32 rows are widened at each use: hoisted out of the step loop, the
   // conversions would take twice the registers.
@@ -547,8 +539,14 @@ __device__ __forceinline__ bool cg_sync(const SolveArgs& a, unsigned& epoch, int
 
 // GRAM: the inner CG applies (SA)^T SA through the precomputed H (owners form
 // their entries of q directly); otherwise through two passes over SA rows.
+//
+// Up to 512 columns two workgroups share a CU (256 registers): the gradient pass of a tall
+// matrix then has twice the rows in flight (536870 x 500 FP64, 300 rows of SA, 8 outer steps:
+// 5.0 ms with one, 2.9 with two).  Only the streaming forms of 257 to 512 columns have to be
+// held to it (28 to 44 bytes of spills with an FP32 operator); asked of the narrower ones, which
+// need fewer anyway, the bound only costs the CG schedule (4096 x 256: 4.9 against 4.5 ms).
 template <typename TA, typename TS, typename TV, int EPT, bool GRAM, bool RES>
-__global__ __launch_bounds__(kBlock) void solve_kernel(SolveArgs a) {
+__global__ __launch_bounds__(kBlock, EPT == 8 && !GRAM ? 2 : 1) void solve_kernel(SolveArgs a) {
   // a driver that enqueues several solves ahead stops them once it is done
   if (a.skip && __hip_atomic_load(a.skip, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
   extern __shared__ double smem[];
@@ -565,7 +563,7 @@ __global__ __launch_bounds__(kBlock) void solve_kernel(SolveArgs a) {
   __shared__ double s_red[2 * kWavesPerBlock];
   __shared__ double s_part[2 * kQuarterRows * kWavesPerBlock];  // rowpass_quarters exchange
   constexpr int EQ = EPT >= 4 ? EPT / 4 : 1;
-  constexpr int NR = resident_rows(sizeof(TS), EPT);
+  constexpr int NR = resident_rows(sizeof(TS), EPT, GRAM);
   // tagged exchanges: the Gram forms up to 2048 columns, the streaming ones up to 1024
   // (2048 spilled 100 registers: Primal-Dual 16384 x 4096 59.7 against 54.7 ms by barrier)
   // (FP64 rows of 2048 entries fill the registers: by barrier)
@@ -655,10 +653,13 @@ __global__ __launch_bounds__(kBlock) void solve_kernel(SolveArgs a) {
     if (in_cg) {
       ResidentRows<TS, EQ, NR> res;
       if constexpr (RES) {
-        if (GRAM)
-          res.load(Hrows, ldhr, 0, nown, d);
-        else
-          res.load(SA, a.ldsa, s_r0, s_r1, d);
+        // (opaque: as loop invariants the rows' addresses and bounds would be kept, or spilled,
+        // across the gradient pass)
+        const TS* M = GRAM ? Hrows : SA + s_r0 * a.ldsa;
+        int64_t ldm = GRAM ? ldhr : a.ldsa;
+        int nrows = GRAM ? nown : (int)(s_r1 - s_r0), dd = d;
+        asm volatile("" : "+s"(M), "+s"(ldm), "+s"(nrows), "+s"(dd));
+        res.load(M, ldm, 0, nrows, dd);
       }
       // colbuf[i] = row i of H . v for the owned rows (thread i < nown reads its own; the
       // barrier inside orders the rest)
@@ -767,7 +768,7 @@ __global__ __launch_bounds__(kBlock) void solve_kernel(SolveArgs a) {
         };
         auto put_scalars = [&](double s0, double s1) {
           if (tid < 2)
-            tagged_put(a.tags + 2 * (((int64_t)scalar_slot(tag) * Gc + w) * 2 + tid),
+            tagged_put(a.tags + (scalar_slot(tag) * (4u * Gc) + (4u * w + 2u * tid)),
                        tid ? s1 : s0, tag);
         };
         // sums of the workgroups' scalars under the current tag, for this wave (lane l
@@ -781,7 +782,7 @@ __global__ __launch_bounds__(kBlock) void solve_kernel(SolveArgs a) {
           for (int i = 0; i < SL; ++i) {
             const int q = lane + i * kWave;
             on[2 * i] = on[2 * i + 1] = q < Gc;
-            ps[2 * i] = a.tags + 2 * (((int64_t)scalar_slot(tag) * Gc + (q < Gc ? q : 0)) * 2);
+            ps[2 * i] = a.tags + (scalar_slot(tag) * (4u * Gc) + 4u * (q < Gc ? q : 0));
             ps[2 * i + 1] = ps[2 * i] + 2;
           }
           if (!tagged_get<2 * SL>(ps, on, tag, v, a.err, a.spin_fast)) {
@@ -803,7 +804,7 @@ __global__ __launch_bounds__(kBlock) void solve_kernel(SolveArgs a) {
         auto exchange = [&](double v, double s0, double s1, double (&x)[NPT], double& t0,
                             double& t1) {
           ++tag;
-          tagged_t* tv = a.tagw + 2 * (int64_t)vector_slot(tag) * a.dpad;
+          tagged_t* tv = a.tagw + vector_slot(tag) * (2u * a.dpad);
           if (own) tagged_put(tv + 2 * (c_lo + tid), v, tag);
           put_scalars(s0, s1);
           // the vector first, then the scalars (polled together: 4096 x 256 5.26 instead of

@@ -13,10 +13,13 @@ constexpr int kMaxBlocksPerCU = 2;
 constexpr size_t kSolveLds = 152 * 1024;  // dynamic LDS at most (the kernel has up to 3 KB more)
 
 // Rows of the inner operator that a workgroup keeps in registers (one quarter of each row per
-// wave, `ept / 4` entries per lane): 256 registers per lane, at most 16 rows.
-constexpr int resident_rows(int bytes, int ept) {
+// wave, `ept / 4` entries per lane): 256 registers per lane, at most 16 rows; 8 streamed rows of
+// 4096 columns in either type, as SA^T u is accumulated beside them (16 FP32 rows spilled 1.2 KB
+// per lane: 16384 x 4096 with 2457 rows of SA, 76 CG steps, 4.4 ms, and 3.2 with rows read in
+// every step).
+constexpr int resident_rows(int bytes, int ept, bool gram) {
   const int eq = ept >= 4 ? ept / 4 : 1;
-  int r = 16;
+  int r = !gram && ept == 64 ? 8 : 16;
   while (r * eq * bytes / 4 > 256) r /= 2;
   return r;
 }
@@ -27,7 +30,7 @@ constexpr int resident_rows(int bytes, int ept) {
 // form that reads H in every step is left for the widths that a partition's CUs may not hold
 // (the smallest has 32: d > 512).
 constexpr bool solve_instance(int bytes, int ept, bool gram, bool res) {
-  return !gram || (res ? resident_rows(bytes, ept) == 16 : ept >= 16);
+  return !gram || (res ? resident_rows(bytes, ept, true) == 16 : ept >= 16);
 }
 
 // Size of the inner-solve subgroup.  With the operator's rows in registers (`res`) it is the
@@ -71,7 +74,7 @@ SolveShape pick_solve_shape(int64_t n, int64_t d, int64_t m, int bytes, int ept,
   // and >= 64 before a CU takes a second one (more partial vectors to add)
   const int64_t g16 = (n + 15) / 16, g64 = (n + 63) / 64;
   const int64_t g_rows = std::max<int64_t>(1, std::min(g16, std::max<int64_t>(g64, num_cu)));
-  const int NR = resident_rows(bytes, ept);
+  const int NR = resident_rows(bytes, ept, gram);
   for (int res = 1; res >= 0; --res) {
     if (!solve_instance(bytes, ept, gram, res != 0)) continue;
     // a Gram matrix is as large as d says, however few rows A has (Primal-Dual solves may have

@@ -21,7 +21,7 @@ int main() {
                 const bool gram = !streamed && m >= d;
                 int ept = 1;
                 while (64 * (int64_t)ept < d) ept *= 2;
-                const int NR = resident_rows(bytes, ept);
+                const int NR = resident_rows(bytes, ept, gram);
                 bool asked_missing = false;
                 const SolveShape S = pick_solve_shape(
                     n, d, m, bytes, ept, gram, cus, [&](bool res, size_t) {

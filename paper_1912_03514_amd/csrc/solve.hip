@@ -127,55 +127,6 @@ SolveKernel pick_kernel(int a_f32, int mixed, int ept, bool gram, bool res) {
   return pick_kernel_typed<float, float>(ept, gram, res);
 }
 
-// The CG goes through the Gram matrix when it is no larger than SA (m >= d).
-bool use_gram(int64_t m, int64_t d) { return m >= d; }
-
-struct SolveLayout {
-  size_t partA, partS, scal, vecs, xp, bar, tags, tagw, gram, yrow, total;
-};
-
-// Barrier region: line 0 = top counter of the all-workgroup barrier, lines 1-8
-// its group counters, line 9 = inner-solve group counter, line 10 = error flag,
-// line 11 = status word, lines 12-20 = top and group counters of the two-level
-// inner-solve barrier (128-byte lines).
-constexpr size_t kBarLines = 21;
-
-// The CG's vector travels as tagged values up to this many columns, by barrier above: every
-// workgroup polls all of it at twice its size (256 workgroups, a round of 2048 values: 3.4 us
-// tagged, 3.9 by barrier; of 4096: 5.1 against 4.3).
-constexpr int64_t kTagCols = 2048;
-
-// Tagged partial vectors of the streaming solvers; they take the Gram matrix's place.
-size_t part_tag_bytes(int Gc, int64_t dpad) {
-  return dpad <= 1024 ? (size_t)Gc * dpad * 16 : 0;
-}
-
-// gram_bytes: size of the Gram matrix region (the tagged partials when the CG streams SA).
-SolveLayout layout(int G, int Gc, int64_t dpad, size_t gram_bytes, int64_t m) {
-  SolveLayout L;
-  size_t off = 0;
-  L.partA = off; off = align_up(off + (size_t)G * dpad * 8, 256);
-  L.partS = off; off = align_up(off + (size_t)Gc * dpad * 8, 256);
-  L.scal = off;  off = align_up(off + (size_t)G * kScal * 8, 256);
-  L.vecs = off;  off = align_up(off + 4 * (size_t)dpad * 8, 256);
-  L.xp = off;    off = align_up(off + (size_t)dpad * 8, 256);
-  L.bar = off;   off = align_up(off + kBarLines * 128, 256);
-  // tagged scalars and vector entries, cleared with the barrier words by every launch
-  L.tags = off;  off += kScalarSlots * (size_t)Gc * 2 * 16;
-  L.tagw = off;  off += dpad <= kTagCols ? kVectorSlots * (size_t)dpad * 16 : 0;
-  off = align_up(off, 256);
-  L.gram = off;  off = align_up(off + gram_bytes, 256);
-  L.yrow = off;  off = align_up(off + (size_t)m * 8, 256);
-  L.total = off;
-  return L;
-}
-
-size_t gram_bytes_for(int64_t m, int64_t d, int mixed) {
-  if (!use_gram(m, d)) return 0;
-  const size_t dp = (size_t)dpad_for(d);
-  return dp * dp * (mixed ? sizeof(float) : sizeof(double));
-}
-
 int max_grid(const mihs_handle* h) { return h->num_cu * kMaxBlocksPerCU; }
 
 }  // namespace
@@ -205,9 +156,7 @@ int ept_for(int64_t d) {
 size_t solve_workspace_bytes(const mihs_handle* h, int64_t n, int64_t d, int64_t m, int mixed,
                              int no_gram) {
   (void)n;
-  const int G = max_grid(h);
-  const size_t gram = no_gram ? 0 : gram_bytes_for(m, d, mixed);
-  return layout(G, G, dpad_for(d), std::max(gram, part_tag_bytes(G, dpad_for(d))), m).total;
+  return solve_layout_bound(max_grid(h), d, m, mixed ? 4 : 8, no_gram != 0);
 }
 
 int grad_partials(const mihs_handle* h, int64_t n, int64_t d) {
@@ -267,12 +216,9 @@ int launch_solve(const mihs_handle* h, const SolveDesc& s, void* ws, size_t ws_b
   if (shape.G == 0) return MIHS_ERR_UNSUPPORTED;
   const int G = shape.G, Gc = shape.Gc, cpw = shape.cpw;
   const size_t shmem = shape.lds;
-  // tagged exchange of the streaming solvers: rows in registers, at most 16 owned columns and
-  // 64 workgroups (what one round of the owners' thread grid reads)
-  const bool tag_sa = !gram && shape.res && ept <= 16 && cpw <= 16 && Gc <= 64;
-  const size_t region = gram ? gram_bytes_for(s.m, s.d, s.mixed)
-                             : (tag_sa ? part_tag_bytes(Gc, dpad) : 0);
-  const SolveLayout L = layout(G, Gc, dpad, region, s.m);
+  const SolveTags tags = solve_tags(gram, shape.res, s.mixed ? 4 : 8, ept, Gc, cpw);
+  const SolveLayout L = solve_layout(G, Gc, dpad, tags, gram ? gram_bytes(s.d, s.mixed ? 4 : 8) : 0,
+                                     s.m);
   if (ws_bytes < L.total || ws == nullptr) return MIHS_ERR_WORKSPACE;
 
   char* base = (char*)ws;
@@ -319,13 +265,13 @@ int launch_solve(const mihs_handle* h, const SolveDesc& s, void* ws, size_t ws_b
   a.Gc = Gc;
   a.cpw = cpw;
   a.tags = (tagged_t*)(base + L.tags);
-  a.tagw = dpad <= kTagCols ? (tagged_t*)(base + L.tagw) : nullptr;
-  a.partT = tag_sa ? (tagged_t*)(base + L.gram) : nullptr;
+  a.tagw = (tagged_t*)(base + L.tagw);
+  a.partT = tags == SolveTags::kStreaming ? (tagged_t*)(base + L.region) : nullptr;
   a.spin_fast.limit = 1L << 26;  // ~64-clock polls: a few seconds at most
   a.spin_fast.sleep = 1;
   a.spin_idle.limit = 1L << 24;  // ~1000-clock polls while the inner solve runs
   a.spin_idle.sleep = 16;
-  a.H = gram ? (const void*)(base + L.gram) : nullptr;
+  a.H = gram ? (const void*)(base + L.region) : nullptr;
   a.ldh = dpad;
   // One barrier per CG step pays off where the CG is latency-bound (headline,
   // FP64: 32.2 -> 29.4 ms per solve); the two-reduction form keeps fewer steps
@@ -337,13 +283,13 @@ int launch_solve(const mihs_handle* h, const SolveDesc& s, void* ws, size_t ws_b
   a.yrow = (double*)(base + L.yrow);
   a.skip = s.skip;
   if (gram && !s.gram_ready) {
-    const int rc = launch_gram(s.SA, s.mixed, s.m, s.d, s.ldsa, base + L.gram, s.mixed, dpad,
+    const int rc = launch_gram(s.SA, s.mixed, s.m, s.d, s.ldsa, base + L.region, s.mixed, dpad,
                                stream);
     if (rc) return rc;
   }
 
-  // barrier words and, where used, tags (contiguous)
-  const int zwords = (int)(((gram ? L.gram : tag_sa ? L.gram + region : L.tags) - L.bar) / 4);
+  // barrier words and tags (contiguous)
+  const int zwords = (int)((L.zero_end - L.bar) / 4);
   hipLaunchKernelGGL(zero_words, dim3((unsigned)((zwords + 1023) / 1024)), dim3(256), 0, stream,
                      bar, zwords);
   if (hipGetLastError() != hipSuccess) return MIHS_ERR_HIP;

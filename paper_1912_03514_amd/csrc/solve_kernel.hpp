@@ -39,7 +39,7 @@
 
 namespace mihs {
 
-constexpr int kScal = 8;           // scalar partial slots per workgroup
+constexpr int kScal = 8;           // scalar partial slots per workgroup (solve_layout)
 constexpr double kCg1MaxCond = 1e5;  // single-reduction CG up to this trace(H)/lambda
 // Rows per group in rowpass_quarters: 128 KB of a 4096-wide matrix in flight per CU in
 // either type (FP32, 2^20 x 4096: 4 rows with the next group prefetched 3.35 ms a pass,
@@ -86,7 +86,7 @@ struct SolveArgs {
   int d, dpad, G, Gc, cpw;
   int cg_hier;        // inner-solve group large enough for the two-level barrier
   int32_t xw[kXcds];  // gradient-pass row weight of each XCD (row_split_bound)
-  tagged_t* tagw;     // kVectorSlots x dpad tagged vector entries (null: by barrier)
+  tagged_t* tagw;     // kVectorSlots x dpad tagged vector entries
   tagged_t* tags;     // kScalarSlots x Gc x 2 tagged scalars
   tagged_t* partT;    // Gc x dpad tagged partials of SA^T u (null: by barrier, partS)
   BarrierSpin spin_fast, spin_idle;
@@ -564,10 +564,10 @@ __global__ __launch_bounds__(kBlock, EPT == 8 && !GRAM ? 2 : 1) void solve_kerne
   __shared__ double s_part[2 * kQuarterRows * kWavesPerBlock];  // rowpass_quarters exchange
   constexpr int EQ = EPT >= 4 ? EPT / 4 : 1;
   constexpr int NR = resident_rows(sizeof(TS), EPT, GRAM);
-  // tagged exchanges: the Gram forms up to 2048 columns, the streaming ones up to 1024
-  // (2048 spilled 100 registers: Primal-Dual 16384 x 4096 59.7 against 54.7 ms by barrier)
-  // (FP64 rows of 2048 entries fill the registers: by barrier)
-  constexpr bool TAGGED = GRAM && RES && EPT * (int)sizeof(TS) < 256, TAGGED_SA = !GRAM && RES && EPT <= 16;
+  // (streaming at 2048 columns spilled 100 registers: Primal-Dual 16384 x 4096 59.7 against 54.7
+  // ms by barrier)
+  constexpr bool TAGGED = GRAM && RES && tagged_gram(sizeof(TS), EPT);
+  constexpr bool TAGGED_SA = !GRAM && RES && tagged_streaming(EPT);
   __shared__ double s_res[kResParts * NR];  // resident rows' partial products
   __shared__ double s_u[NR], s_y[NR];       // SA rows: u of this step, y of the last one
   __shared__ int s_flag;

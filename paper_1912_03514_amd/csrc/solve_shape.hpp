@@ -1,11 +1,13 @@
-// Launch shape of the persistent solve (host only, no HIP calls): which form of the kernel runs,
-// on how many workgroups, and with how much LDS.
+// Launch shape and workspace of the persistent solve (host only, no HIP calls): which form of the
+// kernel runs, on how many workgroups, with how much LDS, and where its scratch lies.
 #pragma once
 
 #include <stddef.h>
 #include <stdint.h>
 
 #include <algorithm>
+
+#include "internal.hpp"
 
 namespace mihs {
 
@@ -102,6 +104,85 @@ SolveShape pick_solve_shape(int64_t n, int64_t d, int64_t m, int bytes, int ept,
     }
   }
   return S;
+}
+
+// ---- workspace ------------------------------------------------------------------
+
+// The CG goes through the Gram matrix when it is no larger than SA (m >= d).
+inline bool use_gram(int64_t m, int64_t d) { return m >= d; }
+
+inline size_t gram_bytes(int64_t d, int bytes) {
+  int64_t dp = 64;
+  while (dp < d) dp *= 2;
+  return (size_t)dp * dp * bytes;
+}
+
+// Which exchanges go by tagged words instead of barriers: those of the CG on a resident Gram
+// matrix up to 2048 columns (FP64 rows of 2048 entries fill the registers: by barrier; every
+// workgroup polls the whole vector at twice its size: 256 workgroups, a round of 2048 values 3.4
+// us tagged, 3.9 by barrier; of 4096 5.1 against 4.3), and those of the streaming solvers on
+// resident rows up to 1024 columns, at most 16 owned columns and 64 workgroups (what one round of
+// the owners' thread grid reads).
+enum class SolveTags { kNone, kGram, kStreaming };
+constexpr bool tagged_gram(int bytes, int ept) { return ept * bytes < 256; }
+constexpr bool tagged_streaming(int ept) { return ept <= 16; }
+inline SolveTags solve_tags(bool gram, bool res, int bytes, int ept, int Gc, int cpw) {
+  if (!res) return SolveTags::kNone;
+  if (gram) return tagged_gram(bytes, ept) ? SolveTags::kGram : SolveTags::kNone;
+  return tagged_streaming(ept) && cpw <= 16 && Gc <= 64 ? SolveTags::kStreaming : SolveTags::kNone;
+}
+
+struct SolveLayout {
+  size_t partA, partS, scal, vecs, xp, bar, tags, tagw, region, yrow, total;
+  size_t zero_end;  // every launch clears [bar, zero_end)
+};
+
+// Barrier region: line 0 = top counter of the all-workgroup barrier, lines 1-8
+// its group counters, line 9 = inner-solve group counter, line 10 = error flag,
+// line 11 = status word, lines 12-20 = top and group counters of the two-level
+// inner-solve barrier (128-byte lines).
+constexpr size_t kBarLines = 21;
+
+// gram: bytes of the Gram matrix (0 when SA is streamed).  Its place is taken by the tagged
+// partial vectors of the streaming solvers.
+inline SolveLayout solve_layout(int G, int Gc, int64_t dpad, SolveTags tags, size_t gram,
+                                int64_t m) {
+  SolveLayout L;
+  size_t off = 0;
+  L.partA = off; off = align_up(off + (size_t)G * dpad * 8, 256);
+  L.partS = off; off = align_up(off + (size_t)Gc * dpad * 8, 256);
+  L.scal = off;  off = align_up(off + (size_t)G * 8 * 8, 256);
+  L.vecs = off;  off = align_up(off + 4 * (size_t)dpad * 8, 256);
+  L.xp = off;    off = align_up(off + (size_t)dpad * 8, 256);
+  L.bar = off;   off = align_up(off + kBarLines * 128, 256);
+  L.tags = off;
+  if (tags != SolveTags::kNone) off += kScalarSlots * (size_t)Gc * 2 * 16;
+  L.tagw = off;
+  if (tags != SolveTags::kNone) off += kVectorSlots * (size_t)dpad * 16;
+  off = align_up(off, 256);
+  const size_t part = tags == SolveTags::kStreaming ? (size_t)Gc * dpad * 16 : 0;
+  L.region = off;
+  L.zero_end = off + part;
+  off = align_up(off + std::max(gram, part), 256);
+  L.yrow = off;  off = align_up(off + (size_t)m * 8, 256);
+  L.total = off;
+  return L;
+}
+
+// Workspace of any launch at these sizes on at most G workgroups, by whichever inner solver and
+// from whatever A: without tags the inner group may be the whole grid, with them it is small.
+inline size_t solve_layout_bound(int G, int64_t d, int64_t m, int bytes, bool no_gram) {
+  int ept = 1;
+  while (64 * (int64_t)ept < d) ept *= 2;
+  const int64_t dpad = 64 * (int64_t)ept;
+  const size_t gram = !no_gram && use_gram(m, d) ? gram_bytes(d, bytes) : 0;
+  size_t most = solve_layout(G, G, dpad, SolveTags::kNone, gram, m).total;
+  if (gram && tagged_gram(bytes, ept))
+    most = std::max(most, solve_layout(G, std::min(G, 128), dpad, SolveTags::kGram, gram, m).total);
+  if (tagged_streaming(ept))
+    most = std::max(most,
+                    solve_layout(G, std::min(G, 64), dpad, SolveTags::kStreaming, gram, m).total);
+  return most;
 }
 
 }  // namespace mihs

@@ -41,6 +41,18 @@ int main() {
                   // the owned rows of a resident Gram matrix are those that are kept
                   if (S.res && gram) ok = ok && S.cpw <= NR && S.cpw <= 16;
                 }
+                // the workspace query covers the launch, and on a whole GPU the tagged exchanges
+                // fit what the barrier forms take on the largest grid
+                const int64_t dpad = 64 * (int64_t)ept;
+                const size_t full = gram ? gram_bytes(d, bytes) : 0;
+                const size_t bound = solve_layout_bound(cus * kMaxBlocksPerCU, d, m, bytes, streamed);
+                if (S.G > 0)
+                  ok = ok && solve_layout(S.G, S.Gc, dpad,
+                                          solve_tags(gram, S.res, bytes, ept, S.Gc, S.cpw), full,
+                                          m).total <= bound;
+                if (cus == 256)
+                  ok = ok && bound == solve_layout(2 * cus, 2 * cus, dpad, SolveTags::kNone,
+                                                   !streamed && m >= d ? full : 0, m).total;
                 // a whole GPU keeps every Gram matrix that fits the registers
                 if (gram && cus == 256 && solve_instance(bytes, ept, true, true)) ok = ok && S.res;
                 if (!ok && ++failures < 20)
@@ -48,6 +60,16 @@ int main() {
                           "cpw %d res %d\n", cus, occ, bytes, (long long)n, (long long)d,
                           (long long)m, gram, S.G, S.Gc, S.cpw, S.res);
               }
+  // the static scratch of 64 MiB holds what it did: d = 2048, FP64, a Gram matrix, and as many
+  // rows of SA (8 bytes of scratch each) as fill it
+  {
+    const size_t scratch = (size_t)64 << 20;
+    const size_t base = 2 * (size_t)512 * 2048 * 8 + 512 * 64 + 5 * 2048 * 8 + 21 * 128 + 128 +
+                        (size_t)2048 * 2048 * 8;
+    const int64_t m = (int64_t)((scratch - base) / 8);
+    if (solve_layout_bound(512, 2048, m, 8, false) > scratch) ++failures;
+    if (solve_layout_bound(512, 2048, m + 64, 8, false) <= scratch) ++failures;
+  }
   // the Primal-Dual dual steps of 100 columns and 200 sketch rows, on a GPU and on a partition
   for (int cus : {32, 256}) {
     const SolveShape S = pick_solve_shape(100, 200, 200, 8, 4, true, cus,

@@ -1,4 +1,4 @@
-"""The launch shape of the persistent solve for every size, form and device size that the entry
+"""The launch shape and workspace of the persistent solve for every size, form and device size that the entry
 points accept (tests/shape_checks.cpp; host code only)."""
 import os
 import shutil
@@ -13,7 +13,8 @@ CXX = os.environ.get("CXX", "g++")
 @pytest.mark.skipif(shutil.which(CXX) is None, reason="no host C++ compiler")
 def test_every_accepted_call_has_a_shape(tmp_path):
     exe = tmp_path / "shape_checks"
-    r = subprocess.run([CXX, "-std=c++17", "-O1", "-Wall",
+    r = subprocess.run([CXX, "-std=c++17", "-O1", "-Wall", "-D__HIP_PLATFORM_AMD__",
+                        "-I/opt/rocm/include",
                         os.path.join(ROOT, "tests", "shape_checks.cpp"), "-o", str(exe)],
                        capture_output=True, text=True)
     assert r.returncode == 0, r.stderr

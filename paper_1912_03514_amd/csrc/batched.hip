@@ -2060,10 +2060,8 @@ int plan_block(const mihs_handle* h, const BlockEntryDesc* ents, int64_t count, 
   a.tol = tol;
   a.max_outer = max_outer;
   a.max_inner = max_inner;
-  a.spin.limit = 1L << 26;
-  a.spin.sleep = 1;
-  a.spin_idle.limit = 1L << 24;
-  a.spin_idle.sleep = 16;
+  a.spin = {kBarrierPolls, 1, kTagPolls};
+  a.spin_idle = {kIdlePolls, 16, kTagPolls};
   *out = P;
   return MIHS_OK;
 }

@@ -232,13 +232,24 @@ __device__ __forceinline__ void clear_tail(int first, int d, int lane, T (&rows)
 // every line the workgroups were reusing, a Gram matrix re-read by every CG
 // step, had to come back from memory after each barrier.)
 //
-// The waits are bounded: after `spin.limit` polls a barrier records a timeout
-// in *err and returns false, so no wave can hang; callers then leave the
-// kernel.
+// The waits are bounded: after `spin.limit` polls (`spin.tag_limit` of a tagged value) a wait
+// records a timeout in *err and returns false, so no wave can hang; callers then leave the
+// kernel.  Every 1024 failed polls a waiter also looks whether somebody else has given up.
 struct BarrierSpin {
   long limit;
   int sleep;  // s_sleep argument between polls (x64 clocks)
+  long tag_limit;
 };
+
+// A wait that has failed `spins` times: true when it is to be given up.
+__device__ __forceinline__ bool poll_spent(unsigned spins, long limit, int* err) {
+  if (spins & 1023u) return false;
+  if ((long)spins < limit &&
+      __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0)
+    return false;
+  atomicOr(err, 1);
+  return true;
+}
 
 template <typename T>
 __device__ __forceinline__ T co_load(const T* p) {
@@ -254,16 +265,13 @@ __device__ __forceinline__ void co_store(T* p, T v) {
 
 __device__ __forceinline__ bool wait_counter(const unsigned* counter, unsigned target, int* err,
                                              BarrierSpin spin) {
-  long spins = 0;
+  unsigned spins = 0;
   while (__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
     if (spin.sleep >= 16)
       __builtin_amdgcn_s_sleep(16);
     else
       __builtin_amdgcn_s_sleep(1);
-    if (++spins > spin.limit) {
-      atomicOr(err, 1);
-      return false;
-    }
+    if (poll_spent(++spins, spin.limit, err)) return false;
   }
   return true;
 }
@@ -338,14 +346,14 @@ __device__ __forceinline__ void tagged_put(tagged_t* p, double v, unsigned tag) 
   co_store(p + 1, t | (b >> 32));
 }
 
-// Values of several words (those that are `on`), all polled together.  Bounded: after
-// `spin.limit` polls records a timeout in *err and returns false.
+// Values of several words (those that are `on`), all polled together.  Bounded: false after a
+// timeout, here or elsewhere.
 template <int N>
 __device__ __forceinline__ bool tagged_get(const tagged_t* const (&p)[N], const bool (&on)[N],
                                            unsigned tag, double (&v)[N], int* err,
                                            BarrierSpin spin) {
   tagged_t lo[N], hi[N];
-  for (long spins = 0;; ++spins) {
+  for (unsigned spins = 1;; ++spins) {
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       lo[i] = on[i] ? co_load(p[i]) : (tagged_t)tag << 32;
@@ -356,10 +364,7 @@ __device__ __forceinline__ bool tagged_get(const tagged_t* const (&p)[N], const 
     for (int i = 0; i < N; ++i)
       ready = ready && (unsigned)(lo[i] >> 32) == tag && (unsigned)(hi[i] >> 32) == tag;
     if (ready) break;
-    if (spins > spin.limit) {
-      atomicOr(err, 1);
-      return false;
-    }
+    if (poll_spent(spins, spin.tag_limit, err)) return false;
   }
 #pragma unroll
   for (int i = 0; i < N; ++i)

@@ -81,6 +81,12 @@ constexpr unsigned kScalarSlots = 4, kVectorSlots = 2;
 MIHS_HOST_DEVICE constexpr unsigned scalar_slot(unsigned tag) { return tag % kScalarSlots; }
 MIHS_HOST_DEVICE constexpr unsigned vector_slot(unsigned tag) { return tag % kVectorSlots; }
 
+// Polls after which the persistent kernels' waits give up.  A poll is a round trip to memory,
+// about a microsecond: a barrier among workgroups that all work waits for about a minute, one
+// that idles during an inner solve (polls of 1000 clocks more) for half a minute, and a tagged
+// value, which only ever waits for the other workgroups' present step, for some five seconds.
+constexpr long kBarrierPolls = 1L << 26, kIdlePolls = 1L << 24, kTagPolls = 1L << 22;
+
 // Measures each XCD's streaming time and sets h->row_weight from it
 // (mihs_calibrate_rows).
 int calibrate_rows(mihs_handle* h);

@@ -267,10 +267,8 @@ int launch_solve(const mihs_handle* h, const SolveDesc& s, void* ws, size_t ws_b
   a.tags = (tagged_t*)(base + L.tags);
   a.tagw = (tagged_t*)(base + L.tagw);
   a.partT = tags == SolveTags::kStreaming ? (tagged_t*)(base + L.region) : nullptr;
-  a.spin_fast.limit = 1L << 26;  // ~64-clock polls: a few seconds at most
-  a.spin_fast.sleep = 1;
-  a.spin_idle.limit = 1L << 24;  // ~1000-clock polls while the inner solve runs
-  a.spin_idle.sleep = 16;
+  a.spin_fast = {kBarrierPolls, 1, kTagPolls};
+  a.spin_idle = {kIdlePolls, 16, kTagPolls};
   a.H = gram ? (const void*)(base + L.region) : nullptr;
   a.ldh = dpad;
   // One barrier per CG step pays off where the CG is latency-bound (headline,

@@ -135,6 +135,12 @@ static size_t stuck_states(const Waves& w, size_t& seen_count) {
   return stuck;
 }
 
+// a poll takes about a microsecond: a tagged wait that will not end is given up within ten
+// seconds, any other within two minutes
+static_assert(mihs::kTagPolls <= 10000000 && mihs::kIdlePolls <= mihs::kBarrierPolls &&
+                  mihs::kBarrierPolls <= 120000000,
+              "bounds of the waits");
+
 int main(int argc, char** argv) {
   scal_slots = argc > 1 ? (unsigned)atoi(argv[1]) : mihs::kScalarSlots;
   vec_slots = argc > 2 ? (unsigned)atoi(argv[2]) : mihs::kVectorSlots;

@@ -523,28 +523,46 @@ __global__ void zero_u32_kernel(unsigned* p, int64_t count) {
 
 // ---------------------------------------------------------------------------
 // CountSketch: h = murmur3(i, seed), bucket = h mod m, sign = -1 iff bit 31.
-// One kernel hashes the rows into per-bucket slot lists; then each (bucket,
-// column block) sorts its list ascending in LDS and sums its rows in that
-// order, so the result does not depend on scheduling.  A row's sign is hashed
-// again where the row is summed (scalar work, one hash per wave and row).
+// One kernel hashes the rows into slot lists, one per bucket and range of rows;
+// then each (bucket, column block) sorts its lists ascending in LDS, range after
+// range, and sums its rows in that order, so the result does not depend on
+// scheduling.  A row's sign is hashed again where the row is summed (scalar
+// work, one hash per wave and row).
 //
 // Bound: one read of A.  Slots of a fixed capacity need neither an offset scan
 // nor a scatter launch with atomics of its own, and the list comes from LDS,
 // so that the rows' 16-byte loads depend on nothing else:
 // 500009 x 1000 FP32, m = 4000: 508 us with separate hash, scan, scatter, sort
-// and 4-byte-load sum kernels.
+// and 4-byte-load sum kernels, 400 now.  The work stays proportional to the rows at any number
+// per bucket: 2^25 x 16 FP32 into 4500 buckets (7456 rows each, two ranges) 12 ms, 191 when
+// every bucket hashed every row; 2^27 x 8 into 17000 46 ms, 2590 so and 1680 with the serial
+// sort of long lists before.
 // ---------------------------------------------------------------------------
-constexpr int64_t kCsMaxMean = 7168;  // rows per bucket up to which lists are kept
+constexpr int64_t kCsMaxMean = 7168;  // rows per list on average, so that a list fits in LDS
+constexpr int64_t kCsFewBuckets = 100;  // fewer than this, of more rows, hash every row instead
 constexpr int kCsBlock = kBlock;
 constexpr int kCsRankSort = 512;      // lists up to this length are sorted by rank
 
-// Slots per bucket: the mean row count plus eight standard deviations (a bucket that
-// overflows is summed by hashing every row again, see cs_accum_kernel).  0 where the mean
-// is above kCsMaxMean: a list would not fit in LDS.
-int64_t cs_capacity(int64_t n, int64_t m) {
+// Row ranges (a multiple of kCsBlock rows each, but for the last) and the slots of a list: the
+// mean row count plus seven standard deviations and a few, in fours (a list that overflows is replaced by
+// hashing its range again, see cs_accum_kernel).
+struct CsLists {
+  int64_t ranges, rows, cap;
+};
+CsLists cs_lists(int64_t n, int64_t m) {
+  CsLists c;
   const double mean = (double)n / (double)m;
-  if (mean > (double)kCsMaxMean) return 0;
-  return (int64_t)ceil(mean + 8.0 * sqrt(mean)) + 16;
+  // With few buckets, hashing every row once per bucket costs less than the atomics on so few
+  // counters and the sorting (8000 rows per bucket, 300 FP32 columns: 64 buckets 1.65 ms, by
+  // lists 2.0; 128 buckets 2.28 and 2.06); it grows with the square of their number (4096
+  // buckets, 16 columns: 174 and 12 ms).
+  if (mean > (double)kCsMaxMean && m < kCsFewBuckets) return {1, n, 0};
+  c.ranges = (int64_t)ceil(mean / (double)kCsMaxMean);
+  c.rows = ((n + c.ranges - 1) / c.ranges + kCsBlock - 1) / kCsBlock * kCsBlock;
+  c.ranges = (n + c.rows - 1) / c.rows;
+  const double per = (double)std::min(c.rows, n) / (double)m;
+  c.cap = ((int64_t)ceil(per + 7.0 * sqrt(per)) + 6 + 3) / 4 * 4;
+  return c;
 }
 // LDS list length (entries): a power of two for the sort, and room for the rows that the
 // hashing form collects between sums.
@@ -554,15 +572,17 @@ int64_t cs_list_len(int64_t cap) {
   return p;
 }
 
+// hist and slots: [range][bucket]; range_blocks workgroups per range (0: one range)
 __global__ __launch_bounds__(kCsBlock) void cs_hash_kernel(int64_t n, int64_t m, uint32_t seed,
-                                                           unsigned cap, unsigned* hist,
-                                                           unsigned* slots) {
+                                                           unsigned range_blocks, unsigned cap,
+                                                           unsigned* hist, unsigned* slots) {
   const int64_t i = (int64_t)blockIdx.x * kCsBlock + threadIdx.x;
   if (i >= n) return;
   const uint32_t h = murmur3_u32((uint32_t)i, seed);
-  const unsigned bucket = h % (uint32_t)m;
-  const unsigned pos = atomicAdd(&hist[bucket], 1u);
-  if (pos < cap) slots[(int64_t)bucket * cap + pos] = (unsigned)i;
+  int64_t list = h % (uint32_t)m;
+  if (range_blocks) list += blockIdx.x / range_blocks * m;
+  const unsigned pos = atomicAdd(&hist[list], 1u);
+  if (pos < cap) slots[list * cap + pos] = (unsigned)i;
 }
 
 // acc += the rows of list[0..cnt), in order, this thread's V columns.
@@ -596,14 +616,13 @@ __device__ __forceinline__ void cs_add_rows(const TA* __restrict__ A, int64_t ld
 
 // One workgroup per (bucket, kCsBlock * V columns); a thread owns the 16 bytes of A's rows
 // from column c (rows are 16-byte aligned, so the last chunk stays inside a row's span).
-// LDS: 2 * list_len entries.
-template <typename TA, typename TAcc, typename TOut>
-__global__ __launch_bounds__(kCsBlock) void cs_accum_kernel(const TA* __restrict__ A, int64_t lda,
-                                                            int64_t n, int64_t d, int64_t m,
-                                                            uint32_t seed, unsigned cap,
-                                                            int list_len, const unsigned* hist,
-                                                            const unsigned* slots,
-                                                            TOut* __restrict__ out, int64_t ldo) {
+// LDS: 2 * list_len entries.  ONE: a single range of rows (as a loop it costs buckets of a row or
+// two up to 10%: 5000 x 4096 FP64 into 4999 buckets 106 us, 118 as a loop).
+template <typename TA, typename TAcc, typename TOut, bool ONE>
+__global__ __launch_bounds__(kCsBlock) void cs_accum_kernel(
+    const TA* __restrict__ A, int64_t lda, int64_t n, int64_t d, int64_t m, uint32_t seed,
+    unsigned cap, int list_len, const unsigned* hist, const unsigned* slots,
+    TOut* __restrict__ out, int64_t ldo, int ranges, int64_t range_rows) {
   constexpr int V = 16 / (int)sizeof(TA);
   extern __shared__ unsigned cs_lds[];
   unsigned* list = cs_lds;
@@ -615,69 +634,81 @@ __global__ __launch_bounds__(kCsBlock) void cs_accum_kernel(const TA* __restrict
   TAcc acc[V];
 #pragma unroll
   for (int q = 0; q < V; ++q) acc[q] = TAcc(0);
-  const unsigned total = cap ? hist[bucket] : 0xFFFFFFFFu;
-  if (total <= cap) {
-    const int cnt = (int)total;
-    if (cnt <= kCsRankSort) {
-      // each element's rank is the number of smaller ones (all rows differ)
-      for (int i = threadIdx.x; i < cnt; i += kCsBlock) list[i] = slots[(int64_t)bucket * cap + i];
-      __syncthreads();
-      for (int i = threadIdx.x; i < cnt; i += kCsBlock) {
-        const unsigned v = list[i];
-        int rank = 0;
+  auto sum_range = [&](int r) {
+    const int64_t which = ONE ? bucket : (int64_t)r * m + bucket;
+    const unsigned total = cap ? hist[which] : 0xFFFFFFFFu;
+    if (total <= cap) {
+      const unsigned* mine = slots + which * cap;
+      const int cnt = (int)total;
+      if (cnt <= kCsRankSort) {
+        // each element's rank is the number of smaller ones (all rows differ)
+        for (int i = threadIdx.x; i < cnt; i += kCsBlock) list[i] = mine[i];
+        __syncthreads();
+        for (int i = threadIdx.x; i < cnt; i += kCsBlock) {
+          const unsigned v = list[i];
+          int rank = 0;
 #pragma unroll 8
-        for (int j = 0; j < cnt; ++j) rank += list[j] < v;
-        sorted[rank] = v;
-      }
-      __syncthreads();
-    } else {
-      // bitonic, padded to a power of two (at most list_len)
-      int P = 1;
-      while (P < cnt) P <<= 1;
-      for (int i = threadIdx.x; i < P; i += kCsBlock)
-        sorted[i] = i < cnt ? slots[(int64_t)bucket * cap + i] : 0xFFFFFFFFu;
-      __syncthreads();
-      for (int k = 2; k <= P; k <<= 1)
-        for (int j = k >> 1; j > 0; j >>= 1) {
-          for (int i = threadIdx.x; i < P / 2; i += kCsBlock) {
-            const int lo = (i / j) * 2 * j + (i % j), hi = lo + j;
-            const unsigned a = sorted[lo], b = sorted[hi];
-            if ((a > b) == ((lo & k) == 0)) {
-              sorted[lo] = b;
-              sorted[hi] = a;
+          for (int j = 0; j < cnt; ++j) rank += list[j] < v;
+          sorted[rank] = v;
+        }
+        __syncthreads();
+      } else {
+        // bitonic, padded to a power of two (at most list_len)
+        int P = 1;
+        while (P < cnt) P <<= 1;
+        for (int i = threadIdx.x; i < P; i += kCsBlock) sorted[i] = i < cnt ? mine[i] : 0xFFFFFFFFu;
+        __syncthreads();
+        for (int k = 2; k <= P; k <<= 1)
+          for (int j = k >> 1; j > 0; j >>= 1) {
+            for (int i = threadIdx.x; i < P / 2; i += kCsBlock) {
+              const int lo = (i / j) * 2 * j + (i % j), hi = lo + j;
+              const unsigned a = sorted[lo], b = sorted[hi];
+              if ((a > b) == ((lo & k) == 0)) {
+                sorted[lo] = b;
+                sorted[hi] = a;
+              }
             }
+            __syncthreads();
           }
+      }
+      if (on) cs_add_rows<TA, TAcc, V, 8>(A, lda, c, seed, sorted, cnt, acc);
+    } else {
+      // no list: hash every row of the range, collect this bucket's in ascending order and sum
+      // them whenever the list is nearly full
+      const int64_t end = ONE ? n : min(n, (r + 1) * range_rows);
+      const int wave = wave_id(), lane = lane_id();
+      int cnt = 0;
+      for (int64_t r0 = r * range_rows; r0 < end; r0 += kCsBlock) {
+        const int64_t i = r0 + threadIdx.x;
+        const uint32_t h = murmur3_u32((uint32_t)i, seed);
+        const bool match = i < end && h % (uint32_t)m == bucket;
+        const unsigned long long ball = __ballot(match);
+        if (lane == 0) s_cnt[wave] = __popcll(ball);
+        __syncthreads();
+        int off = cnt, all = cnt;
+#pragma unroll
+        for (int w = 0; w < kCsBlock / kWave; ++w) {
+          if (w < wave) off += s_cnt[w];
+          all += s_cnt[w];
+        }
+        if (match)
+          list[off + __popcll(ball & ((1ull << lane) - 1ull))] = (unsigned)i;
+        cnt = all;
+        __syncthreads();
+        if (cnt + kCsBlock > list_len || r0 + kCsBlock >= end) {
+          if (on) cs_add_rows<TA, TAcc, V, 16>(A, lda, c, seed, list, cnt, acc);
+          cnt = 0;
           __syncthreads();
         }
+      }
     }
-    if (on) cs_add_rows<TA, TAcc, V, 8>(A, lda, c, seed, sorted, cnt, acc);
+  };
+  if constexpr (ONE) {
+    sum_range(0);
   } else {
-    // a bucket without a list: hash every row, collect this bucket's in ascending order and
-    // sum them whenever the list is nearly full
-    const int wave = wave_id(), lane = lane_id();
-    int cnt = 0;
-    for (int64_t r0 = 0; r0 < n; r0 += kCsBlock) {
-      const int64_t i = r0 + threadIdx.x;
-      const uint32_t h = murmur3_u32((uint32_t)i, seed);
-      const bool match = i < n && h % (uint32_t)m == bucket;
-      const unsigned long long ball = __ballot(match);
-      if (lane == 0) s_cnt[wave] = __popcll(ball);
-      __syncthreads();
-      int off = cnt, all = cnt;
-#pragma unroll
-      for (int w = 0; w < kCsBlock / kWave; ++w) {
-        if (w < wave) off += s_cnt[w];
-        all += s_cnt[w];
-      }
-      if (match)
-        list[off + __popcll(ball & ((1ull << lane) - 1ull))] = (unsigned)i;
-      cnt = all;
-      __syncthreads();
-      if (cnt + kCsBlock > list_len || r0 + kCsBlock >= n) {
-        if (on) cs_add_rows<TA, TAcc, V, 16>(A, lda, c, seed, list, cnt, acc);
-        cnt = 0;
-        __syncthreads();
-      }
+    for (int r = 0; r < ranges; ++r) {
+      if (r > 0) __syncthreads();  // the last range's rows are summed
+      sum_range(r);
     }
   }
   if (on) {
@@ -1096,15 +1127,16 @@ int run_gauss(const mihs_handle* h, const TB* B, int64_t K, int64_t N, int64_t l
 
 // ---- CountSketch driver -------------------------------------------------------
 struct CsPlan {
-  int64_t cap;  // slots per bucket
+  CsLists lists;
   size_t hist, slots, total;
 };
 CsPlan cs_plan(int64_t n, int64_t m) {
   CsPlan p;
-  p.cap = cs_capacity(n, m);
+  p.lists = cs_lists(n, m);
+  const size_t count = p.lists.cap ? (size_t)p.lists.ranges * m : 0;
   size_t o = 0;
-  p.hist = o; o = align_up(o + (size_t)m * 4, 256);
-  p.slots = o; o = align_up(o + (size_t)m * (size_t)p.cap * 4, 256);
+  p.hist = o; o = align_up(o + count * 4, 256);
+  p.slots = o; o = align_up(o + count * (size_t)p.lists.cap * 4, 256);
   p.total = o;
   return p;
 }
@@ -1116,24 +1148,29 @@ int run_countsketch(const TA* A, int64_t n, int64_t d, int64_t lda, int64_t m, u
   if (ws_bytes < p.total) return MIHS_ERR_WORKSPACE;
   unsigned* hist = (unsigned*)(ws + p.hist);
   unsigned* slots = (unsigned*)(ws + p.slots);
-  const unsigned cap = (unsigned)p.cap;
-  const int list_len = (int)cs_list_len(p.cap);
+  const unsigned cap = (unsigned)p.lists.cap;
+  const int list_len = (int)cs_list_len(p.lists.cap);
   if (cap) {
     // the counts start from zero (a kernel, not a memset: a caller may capture
     // this sequence in a graph)
-    hipLaunchKernelGGL(zero_u32_kernel, dim3((unsigned)ceil_div(m, 256)), dim3(256), 0, st, hist,
-                       m);
+    const int64_t count = p.lists.ranges * m;
+    hipLaunchKernelGGL(zero_u32_kernel, dim3((unsigned)ceil_div(count, 256)), dim3(256), 0, st,
+                       hist, count);
     hipLaunchKernelGGL(cs_hash_kernel, dim3((unsigned)ceil_div(n, kCsBlock)), dim3(kCsBlock), 0,
-                       st, n, m, seed, cap, hist, slots);
+                       st, n, m, seed,
+                       p.lists.ranges > 1 ? (unsigned)(p.lists.rows / kCsBlock) : 0u, cap, hist,
+                       slots);
   }
   const size_t lds = 2 * (size_t)list_len * sizeof(unsigned);
-  auto kern = cs_accum_kernel<TA, TAcc, TOut>;
+  auto kern = p.lists.ranges == 1 ? cs_accum_kernel<TA, TAcc, TOut, true>
+                                  : cs_accum_kernel<TA, TAcc, TOut, false>;
   if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
                           (int)lds) != hipSuccess)
     return MIHS_ERR_HIP;
   const int64_t wide = kCsBlock * (16 / (int64_t)sizeof(TA));
   hipLaunchKernelGGL(kern, dim3((unsigned)m, (unsigned)ceil_div(d, wide)), dim3(kCsBlock), lds, st,
-                     A, lda, n, d, m, seed, cap, list_len, hist, slots, out, ldo);
+                     A, lda, n, d, m, seed, cap, list_len, hist, slots, out, ldo,
+                     (int)p.lists.ranges, p.lists.rows);
   return hip_ok() ? MIHS_OK : MIHS_ERR_HIP;
 }
 

@@ -1208,7 +1208,10 @@ SrhtFusedPlan srht_fused_plan(const mihs_handle* h, int64_t n, int64_t d, int64_
   // Block ranges per strip: one workgroup runs per CU, so strips x ranges workgroups take
   // ceil(that / CUs) rounds of nblk / ranges blocks, and every range writes and reads back
   // its partial sums.  The least of rounds x blocks x ~3 us (a 1024-row FP32 block; twice
-  // that from FP64 rows) plus the partials' bytes at ~4 TB/s.
+  // that from FP64 rows) plus the partials' bytes at ~4 TB/s.  A range's sum runs over its blocks
+  // one by one, so fewer ranges mean longer FP32 sums: against the FP64 form the mixed sketch's
+  // relative error is 1.4e-7 to 2.3e-7 from 65536 x 100 to 2^22 x 40, within 1% of the even split
+  // over the CUs or below it.
   double best = 0.0;
   const int64_t pmax = std::max<int64_t>(32, 2 * ceil_div(h->num_cu, F.strips));
   for (int64_t p = 1; p <= pmax && p <= F.nblk; ++p) {
